@@ -179,7 +179,6 @@ int token_stats(const char* fn, const void* hidden, const void* w_vocab, const i
     a.n_vt = plan.n_vt;
     a.tpc = plan.tpc;
     a.n_ch = plan.n_ch;
-    a.n_grt = lp.n_grt;
     a.part_stride = n;
     a.part_m = part;
     a.part_s = part + plane;
@@ -543,7 +542,6 @@ int hdl_token_logprobs_backward(const void* hidden, const void* w_vocab, const i
       a.n_vt = plan.fwd.n_vt;
       a.tpc = plan.fwd.tpc;
       a.n_ch = plan.fwd.n_ch;
-      a.n_grt = grad_launch.n_grt;
       a.row_base = base;
       a.row_cap = plan.nc;
       a.lse_in = lse_b;

@@ -18,7 +18,7 @@ struct LmheadArgs {
   const int32_t* n_scored;  // device-side count of scored rows
   int64_t d;
   int64_t vocab;
-  int64_t n_vt, tpc, n_ch, n_grt;
+  int64_t n_vt, tpc, n_ch;
   int64_t part_stride;      // elements between chunk planes of the partials
   float* part_m;            // running max (natural-log units)
   float* part_s;            // sum of exp(z - m)

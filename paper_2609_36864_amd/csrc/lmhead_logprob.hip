@@ -111,13 +111,16 @@ __global__ __launch_bounds__(kThreads, 1) void lmhead_logprob_kernel(LmheadArgs 
   const int grp = lane >> 4;    // lane group: K chunk of a fragment, row quad of a result block
 
   // ---- work item: XCD-aware (row tile, vocabulary chunk), see plan.h -----
-  int64_t rt, ch;
-  work_item(blockIdx.x, p.n_grt, &rt, &ch);
   int64_t n_s = *p.n_scored - p.row_base;
   n_s = n_s < 0 ? 0 : (n_s > p.row_cap ? p.row_cap : n_s);
-  const int64_t n_rt = (n_s + kTileN - 1) / kTileN;
+  const ItemGrid items = item_grid(n_s, p.n_ch);
   const int64_t n_s_pad = (n_s + 63) / 64 * 64;   // gradient mode: rows written (row_cap % 64 == 0)
-  if (rt >= n_rt || ch >= p.n_ch) return;
+  int64_t rt, ch;
+  work_item(blockIdx.x, items, &rt, &ch);
+  // (the divisions run on the vector ALU: back to scalar registers)
+  rt = __builtin_amdgcn_readfirstlane(static_cast<int>(rt));
+  ch = __builtin_amdgcn_readfirstlane(static_cast<int>(ch));
+  if (rt >= items.n_rt) return;
 
   const int64_t vt0 = ch * p.tpc;
   const int64_t vt1 = (vt0 + p.tpc < p.n_vt) ? vt0 + p.tpc : p.n_vt;

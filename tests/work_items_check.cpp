@@ -1,0 +1,52 @@
+// CPU check of the work-item order (csrc/plan.h) for any number of scored
+// rows of a launch: every (row tile, chunk) is produced exactly once by the
+// launched workgroups, the XCDs get equal shares (to within one run of 32),
+// and any whole run of 32 items reads at most 20 different tiles (12 in a whole
+// block) once there are that many chunks.
+#include <algorithm>
+#include <cstdio>
+#include <cstdlib>
+#include <set>
+#include <vector>
+
+#include "../paper_2609_36864_amd/csrc/plan.h"
+
+using namespace hdl;
+
+int main(int argc, char** argv) {
+  if (argc != 4) return 2;
+  const int64_t n_rows = std::atoll(argv[1]), vocab = std::atoll(argv[2]), d = std::atoll(argv[3]);
+  const LmheadPlan p = make_plan(n_rows, vocab, d, 2);
+  const LmheadLaunch l = plan_launch(p, n_rows);
+  for (int64_t n_s = 1; n_s <= n_rows; n_s += 1 + n_rows / 61) {
+    const ItemGrid g = item_grid(n_s, p.n_ch);
+    std::vector<int> seen(static_cast<size_t>(g.n_rt * g.n_ch), 0);
+    std::vector<int64_t> share(kNumXcd, 0);
+    for (int64_t b = 0; b < l.grid; ++b) {
+      int64_t rt, ch;
+      work_item(b, g, &rt, &ch);
+      if (rt >= g.n_rt) continue;
+      if (ch < 0 || ch >= g.n_ch || rt < 0) return std::printf("item out of range\n"), 1;
+      ++seen[static_cast<size_t>(rt * g.n_ch + ch)];
+      ++share[b % kNumXcd];
+    }
+    for (int c : seen)
+      if (c != 1) return std::printf("n_s=%lld: an item is taken %d times\n", (long long)n_s, c), 1;
+    const auto mm = std::minmax_element(share.begin(), share.end());
+    if (*mm.second - *mm.first > 32) return std::printf("n_s=%lld: uneven shares\n", (long long)n_s), 1;
+    if (g.n_ch % kGroupCH == 0 && g.n_ch >= 32)
+      for (int64_t run = 0; run < g.n_rt * g.n_ch / 32; ++run) {
+        std::set<int64_t> rts, chs;
+        for (int64_t i = 0; i < 32; ++i) {
+          int64_t rt, ch;
+          work_item(((run / kNumXcd) * 32 + i) * kNumXcd + run % kNumXcd, g, &rt, &ch);
+          rts.insert(rt);
+          chs.insert(ch);
+        }
+        if (g.n_rt >= 3 && rts.size() + chs.size() > 20)
+          return std::printf("n_s=%lld run %lld: %zu + %zu tiles\n", (long long)n_s, (long long)run, rts.size(), chs.size()), 1;
+      }
+  }
+  std::printf("ok\n");
+  return 0;
+}
