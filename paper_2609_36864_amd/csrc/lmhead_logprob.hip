@@ -28,8 +28,9 @@
 // are merged only once per work item.
 //
 // Operands stream through LDS in K-slices of 128 bytes per row (64 bf16 or
-// 32 fp32) through a ring of 2 stages (128 KB): the next slice is in flight
-// (global -> LDS DMA, no VGPR staging) while slice i is multiplied.  16-byte
+// 32 fp32) through a ring of 2 stages (128 KB; more for narrow tiles, see
+// Ring): the next slice is in flight (global -> LDS DMA, no VGPR staging) while
+// slice i is multiplied.  16-byte
 // chunks are XOR swizzled and each lane group reads the chunk frag_chunk()
 // assigns it, so that the 16-row fragment reads are bank-conflict free.
 // The DMA is issued from inline assembly (wave-uniform 64-bit base +
@@ -76,9 +77,12 @@ __device__ __forceinline__ void combine(float& m, float& s, float& z, float& t, 
 static_assert(kKSteps == 2, "a K-slice is two K-steps");
 static_assert(kVB % 2 == 0, "the gradient epilogue pairs vocabulary blocks");
 
-// KTAIL: d is not a multiple of the K-slice, so the last slice of every
-// row needs zero-filling (a separate instantiation keeps that work out of the
-// common case).  EPI selects what each V-tile's logits feed:
+// KTAIL: d is not a multiple of the K-slice, so part of every row's last slice
+// is masked out (a separate instantiation keeps that work out of the common
+// case).  The tail slice runs the same schedule as the others (its W
+// chunks are cleared between two waits that every slice has anyway; with two
+// more barriers per row and the next slice's DMAs issued in one go, 8,192
+// rows at d = 2056, V = 151,936 took 4925 us, now 4836).  EPI selects what each V-tile's logits feed:
 //   kEpiStats:   online max / sum of exp and the sampled-token logit;
 //   kEpiEntropy: the same plus sum exp(z - m) * (z - m) for the next-token
 //                entropy H = ln s - E_p[z - m] (the Entropy localization
@@ -91,41 +95,59 @@ static_assert(kVB % 2 == 0, "the gradient epilogue pairs vocabulary blocks");
 //                contraction over rows can run in whole 64-row K-slices.
 constexpr int kEpiStats = 0, kEpiEntropy = 1, kEpiGrad = 2;
 
-template <bool BF16, bool KTAIL, int EPI>
-__global__ __launch_bounds__(kThreads, 1) void lmhead_logprob_kernel(LmheadArgs p) {
+// Row tiles are 64 TB token rows: TB = 4 (kTileN) for whole tiles, 1 or 2 where
+// no more rows are left or where the chip would idle otherwise (item_grid in
+// plan.h).  The eight waves keep their split of the vocabulary (2 x 128 rows)
+// and share the tokens, 16 TB each, so a row's result has the same bits in
+// any of them.  A narrow tile does little matrix work per K-slice and waits
+// for the slice's 32 KB of W, so it keeps more slices in flight: 4 stages of
+// 32 + 8 KB (TB = 1), 3 of 32 + 16 KB (TB = 2), 2 of 32 + 32 KB (TB = 4).
+// Whole calls at V = 151,936, whole tiles only -> with narrow ones: 16 rows,
+// d 2048 198 -> 165 us; 96 rows 216 -> 183 (W alone, 622 MB, takes 123 us at
+// the 5.05 TB/s a copy reaches); 64 rows, d 4096 378 -> 307; 512 fp32 rows x
+// 4,096 words (32 items on 256 CUs before) 85 -> 40.
+template <int TB>
+struct Ring {
+  static constexpr int kStages = TB == 1 ? 4 : TB == 2 ? 3 : 2;
+  static constexpr int kRowsN = 64 * TB;                      // token rows of the tile
+  static constexpr int kStageSlots = kSlots + kRowsN * kChunks;
+  static constexpr int kBlocksH = TB;                         // hidden-state DMA blocks per wave
+  static constexpr int kDma = kBlocksPerWave + kBlocksH;      // DMA instructions per lane per slice
+  static_assert(kDma * (kStages - 1) <= 63, "vmcnt range");
+};
+constexpr int kLdsSlots = 10240;   // 160 KB
+static_assert(Ring<1>::kStages * Ring<1>::kStageSlots <= kLdsSlots && Ring<2>::kStages * Ring<2>::kStageSlots <= kLdsSlots &&
+                  Ring<4>::kStages * Ring<4>::kStageSlots <= kLdsSlots,
+              "LDS ring exceeds 160 KB");
+
+// One work item: scored rows row0 .. row0 + 64 TB - 1 (of n_s) x chunk ch.
+template <bool BF16, bool KTAIL, int EPI, int TB>
+__device__ __forceinline__ void run_item(const LmheadArgs& p, int64_t row0, int64_t ch, int64_t n_s, uint4* lds) {
   constexpr bool ENT = EPI == kEpiEntropy;
   constexpr bool GRAD = EPI == kEpiGrad;
   using M = Mma16<BF16>;
+  using R = Ring<TB>;
   constexpr int kEsz = BF16 ? 2 : 4;
   constexpr int kElemsPer16B = 16 / kEsz;
   constexpr int kSliceK = kElemsPer16B * kChunks;   // K elements per slice
-
-  __shared__ uint4 lds[kStages][2][kSlots];   // [stage][0 = W, 1 = hidden] = 128 KB
+  constexpr int kWaveRows = 16 * TB;                // token rows per wave
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform
   const int wm = wave & 1;      // which 128 vocabulary rows of the tile
-  const int wn = wave >> 1;     // which kWaveN token rows of the tile
+  const int wn = wave >> 1;     // which kWaveRows token rows of the tile
   const int r16 = lane & 15;    // row of a 16-row fragment / column of a result block
   const int grp = lane >> 4;    // lane group: K chunk of a fragment, row quad of a result block
-
-  // ---- work item: XCD-aware (row tile, vocabulary chunk), see plan.h -----
-  int64_t n_s = *p.n_scored - p.row_base;
-  n_s = n_s < 0 ? 0 : (n_s > p.row_cap ? p.row_cap : n_s);
-  const ItemGrid items = item_grid(n_s, p.n_ch);
   const int64_t n_s_pad = (n_s + 63) / 64 * 64;   // gradient mode: rows written (row_cap % 64 == 0)
-  int64_t rt, ch;
-  work_item(blockIdx.x, items, &rt, &ch);
-  // (the divisions run on the vector ALU: back to scalar registers)
-  rt = __builtin_amdgcn_readfirstlane(static_cast<int>(rt));
-  ch = __builtin_amdgcn_readfirstlane(static_cast<int>(ch));
-  if (rt >= items.n_rt) return;
 
-  const int64_t vt0 = ch * p.tpc;
-  const int64_t vt1 = (vt0 + p.tpc < p.n_vt) ? vt0 + p.tpc : p.n_vt;
+  // (32-bit: a 64-bit minimum would leave these wave-uniform values, and the
+  // loop's branches on them, on the vector ALU; V < 2^31)
+  const int vt0 = static_cast<int>(ch * p.tpc);
+  const int vt1 = vt0 + static_cast<int>(p.tpc) < static_cast<int>(p.n_vt) ? vt0 + static_cast<int>(p.tpc)
+                                                                            : static_cast<int>(p.n_vt);
   const int nk = static_cast<int>((p.d + kSliceK - 1) / kSliceK);
-  const int n_iter = static_cast<int>(vt1 - vt0) * nk;
+  const int n_iter = (vt1 - vt0) * nk;
   const int64_t d = p.d;
   const int64_t V = p.vocab;
 
@@ -133,11 +155,11 @@ __global__ __launch_bounds__(kThreads, 1) void lmhead_logprob_kernel(LmheadArgs 
   const char* __restrict__ hbase = static_cast<const char*>(p.hidden);
 
   // ---- this lane's token columns and their sampled tokens ------------------
-  int tok[kTB];
-  float g_lse[kTB], g_up[kTB];   // gradient mode: lse * log2(e) and upstream gradient
+  int tok[TB];
+  float g_lse[TB], g_up[TB];   // gradient mode: lse * log2(e) and upstream gradient
 #pragma unroll
-  for (int bn = 0; bn < kTB; ++bn) {
-    int64_t e = rt * kTileN + wn * kWaveN + bn * 16 + r16;
+  for (int bn = 0; bn < TB; ++bn) {
+    int64_t e = row0 + wn * kWaveRows + bn * 16 + r16;
     e = e < n_s ? e : n_s - 1;
     const int row = p.rows[e];
     tok[bn] = p.tokens[row];
@@ -149,15 +171,15 @@ __global__ __launch_bounds__(kThreads, 1) void lmhead_logprob_kernel(LmheadArgs 
     }
   }
 
-  float run_m[kTB], run_s[kTB], run_z[kTB], run_t[kTB];
+  float run_m[TB], run_s[TB], run_z[TB], run_t[TB];
 #pragma unroll
-  for (int bn = 0; bn < kTB; ++bn) { run_m[bn] = kNegInf; run_s[bn] = 0.f; run_z[bn] = kNegInf; run_t[bn] = 0.f; }
+  for (int bn = 0; bn < TB; ++bn) { run_m[bn] = kNegInf; run_s[bn] = 0.f; run_z[bn] = kNegInf; run_t[bn] = 0.f; }
 
-  f32x4_t acc[kVB][kTB];
+  f32x4_t acc[kVB][TB];
 #pragma unroll
   for (int bm = 0; bm < kVB; ++bm)
 #pragma unroll
-    for (int bn = 0; bn < kTB; ++bn)
+    for (int bn = 0; bn < TB; ++bn)
 #pragma unroll
       for (int q = 0; q < 4; ++q) acc[bm][bn][q] = 0.f;
 
@@ -167,94 +189,104 @@ __global__ __launch_bounds__(kThreads, 1) void lmhead_logprob_kernel(LmheadArgs 
   // LDS slot l, i.e. row l/kChunks and physical chunk l%kChunks, so it
   // fetches the logical chunk that the read swizzle maps there.
   const int lrow = lane / kChunks;
-  // logical chunk this lane fetches for DMA block i of this wave
-  auto dma_chunk = [&](int i) {
-    const int row = (wave * kBlocksPerWave + i) * kBlockRows + lrow;
-    return (lane % kChunks) ^ row_xor(row);
+  // logical chunk this lane fetches for DMA block `block` of a tile
+  auto dma_chunk = [&](int block) { return (lane % kChunks) ^ row_xor(block * kBlockRows + lrow); };
+  // (KTAIL, rows shorter than a slice: no offset points past the row)
+  const int row_chunks = static_cast<int>(d * kEsz / 16);
+  auto fetch_chunk = [&](int block) {
+    return KTAIL && dma_chunk(block) >= row_chunks ? 0 : dma_chunk(block);
   };
-  constexpr bool k_tail = KTAIL;
   const int64_t row_bytes = d * kEsz;
   // Per-lane byte offsets (row start + 16-byte chunk) of this wave's DMA
   // blocks; a launch never spans more than 4 GiB of hidden states, and W is
   // addressed from the current V-tile's first row.
-  uint32_t hoff[kBlocksPerWave];
+  uint32_t hoff[R::kBlocksH];
 #pragma unroll
-  for (int i = 0; i < kBlocksPerWave; ++i) {
-    int64_t e = rt * kTileN + wave * (kTileN / kWaves) + i * kBlockRows + lrow;
+  for (int i = 0; i < R::kBlocksH; ++i) {
+    int64_t e = row0 + (wave * R::kBlocksH + i) * kBlockRows + lrow;
     e = e < n_s ? e : n_s - 1;
-    hoff[i] = static_cast<uint32_t>(static_cast<int64_t>(p.rows[e]) * row_bytes + dma_chunk(i) * 16);
+    hoff[i] = static_cast<uint32_t>(static_cast<int64_t>(p.rows[e]) * row_bytes + fetch_chunk(wave * R::kBlocksH + i) * 16);
   }
   uint32_t woff[kBlocksPerWave];
   uint64_t wtile = 0;   // address of the current V-tile's first row (uniform)
-  auto set_w = [&](int64_t vt) {
-    wtile = reinterpret_cast<uint64_t>(wbase) + static_cast<uint64_t>(vt * kTileV * row_bytes);
+  auto set_w = [&](int vt) {
+    wtile = uniform64(reinterpret_cast<uint64_t>(wbase) + static_cast<uint64_t>(int64_t{vt} * kTileV * row_bytes));
+    const int last = static_cast<int>(V - 1 - int64_t{vt} * kTileV);   // (rows past V fetch row V - 1)
 #pragma unroll
     for (int i = 0; i < kBlocksPerWave; ++i) {
-      int64_t v = vt * kTileV + wave * (kTileV / kWaves) + i * kBlockRows + lrow;
-      v = v < V ? v : V - 1;
-      woff[i] = static_cast<uint32_t>((v - vt * kTileV) * row_bytes + dma_chunk(i) * 16);
+      const int v = (wave * kBlocksPerWave + i) * kBlockRows + lrow;
+      woff[i] = static_cast<uint32_t>(v < last ? v : last) * static_cast<uint32_t>(row_bytes) +
+                static_cast<uint32_t>(fetch_chunk(wave * kBlocksPerWave + i) * 16);
     }
   };
   const uint32_t lds_base = static_cast<uint32_t>(
-      reinterpret_cast<size_t>((__attribute__((address_space(3))) uint4*)(&lds[0][0][0])));
+      reinterpret_cast<size_t>((__attribute__((address_space(3))) uint4*)lds));
   auto lds_addr = [&](int stage, int op, int block) -> uint32_t {
     return __builtin_amdgcn_readfirstlane(
-        lds_base + static_cast<uint32_t>(((stage * 2 + op) * kSlots + block * 64) * 16));
+        lds_base + static_cast<uint32_t>((stage * R::kStageSlots + op * kSlots + block * 64) * 16));
   };
-  // DMA j (0 .. kDmaPerSlice-1) of K-slice `slice`; j < kBlocksPerWave are W
-  // blocks, the rest hidden-state blocks.  prep_issue() must run first.
+  // DMA j (0 .. R::kDma-1) of a K-slice; j < kBlocksPerWave are W blocks,
+  // the rest hidden-state blocks, of the slice prep_issue() moved to.  The last
+  // K-slice of rows whose length is no multiple of the slice (KTAIL) is the
+  // row's last 128 bytes, so that it needs no addresses of its own; the chunks
+  // that the slice before it holds as well are cleared by clear_w_tail().
   uint32_t issue_kbytes = 0;
-  int issue_stage = 0;
-  bool issue_tail = false;
-  // slot: the ring position (its stage); slice: the data fetched into it
-  // (they differ only for the copies of the last slice past the end)
-  auto prep_issue = [&](int slot, int slice) {
-    issue_stage = slot % kStages;
-    const int kt = slice % nk;
-    if (kt == 0) set_w(vt0 + slice / nk);
-    issue_kbytes = static_cast<uint32_t>(kt) * kSliceK * kEsz;
-    issue_tail = k_tail && kt == nk - 1;
+  int issue_stage = R::kStages - 1;
+  // next_issue() moves on to the next slice and ring stage (scalar work only,
+  // placed early in the slice before it: counters and one branch instead of a
+  // division per slice after the barrier, 1 % at 16,384 rows, d 4096); set_issue() then updates the lanes'
+  // offsets where that slice starts another V-tile.  Past the work item's last
+  // slice the offsets stay on one line of it, so what is fetched then (into
+  // stages nothing reads any more) costs next to nothing.
+  int issue_kt = -1, issue_left = n_iter;
+  int issue_vt = vt0;
+  auto next_stage = [](int st) { return st + 1 == R::kStages ? 0 : st + 1; };
+  auto next_issue = [&]() {
+    issue_stage = next_stage(issue_stage);
+    const bool wrap = ++issue_kt == nk;
+    issue_kt = wrap ? 0 : issue_kt;
+    issue_vt += wrap ? 1 : 0;
+    issue_kbytes = static_cast<uint32_t>(issue_kt) * kSliceK * kEsz;
+    if (KTAIL) {
+      const uint32_t tail = static_cast<uint32_t>(row_bytes) - kSliceK * kEsz;
+      issue_kbytes = issue_kt > 0 && issue_kt == nk - 1 ? tail : issue_kbytes;
+    }
+    --issue_left;
   };
-  auto issue_one = [&](int j, auto tail_tag) {
-    constexpr bool kTail = decltype(tail_tag)::value;
-    const int i = j % kBlocksPerWave;
-    const uint32_t off = j < kBlocksPerWave ? woff[i] : hoff[i];
-    const uint64_t base = j < kBlocksPerWave ? wtile : reinterpret_cast<uint64_t>(hbase);
-    const uint32_t lds = lds_addr(issue_stage, j < kBlocksPerWave ? 0 : 1, wave * kBlocksPerWave + i);
-    if (!kTail) {
-      dma16(base + issue_kbytes, off, lds);
-    } else {
-      // chunks past the end of the row fetch the row start instead (an
-      // in-bounds dummy, zeroed after arrival)
-      const uint32_t chunk_bytes = dma_chunk(i) * 16;
-      const bool in = static_cast<int64_t>(issue_kbytes + chunk_bytes) < row_bytes;
-      dma16(base, off - chunk_bytes + (in ? issue_kbytes + chunk_bytes : 0), lds);
+  auto set_issue = [&]() {
+    if (issue_kt != 0) return;
+    if (issue_left >= 0) {
+      set_w(issue_vt);
+    } else {   // (empty asm: keeps the two branches' stores apart)
+#pragma unroll
+      for (int i = 0; i < kBlocksPerWave; ++i) asm volatile("v_mov_b32 %0, 0" : "=v"(woff[i]));
+#pragma unroll
+      for (int i = 0; i < R::kBlocksH; ++i) asm volatile("v_mov_b32 %0, 0" : "=v"(hoff[i]));
     }
   };
-  auto issue = [&](int slice) {
-    prep_issue(slice, slice);
-    if (!issue_tail) {
-#pragma unroll
-      for (int j = 0; j < kDmaPerSlice; ++j) issue_one(j, std::false_type{});
+  auto issue_one = [&](auto j_tag) {
+    constexpr int j = decltype(j_tag)::value;
+    if constexpr (j < kBlocksPerWave) {
+      dma16(wtile + issue_kbytes, woff[j], lds_addr(issue_stage, 0, wave * kBlocksPerWave + j));
     } else {
-#pragma unroll
-      for (int j = 0; j < kDmaPerSlice; ++j) issue_one(j, std::true_type{});
+      constexpr int i = j - kBlocksPerWave;
+      dma16(reinterpret_cast<uint64_t>(hbase) + issue_kbytes, hoff[i], lds_addr(issue_stage, 1, wave * R::kBlocksH + i));
     }
   };
 
-  // On the last K-slice of a row whose length is not a multiple of the
-  // slice, clear the chunks past d (between two barriers: the DMA of every
-  // wave must have landed before, and no wave may read before it is done).
-  auto clear_k_tail = [&](int slice) {
-    const int stage = slice % kStages;
-    const int kt = slice % nk;
-    for (int sidx = tid; sidx < kSlots; sidx += kThreads) {
-      const int row = sidx / kChunks;
-      const int chunk = (sidx % kChunks) ^ row_xor(row);
-      if (static_cast<int64_t>(kt) * kSliceK + chunk * kElemsPer16B >= d) {
-        lds[stage][0][sidx] = make_uint4(0, 0, 0, 0);
-        lds[stage][1][sidx] = make_uint4(0, 0, 0, 0);
-      }
+  // KTAIL: clears, in a landed last K-slice, the chunks that belong to the
+  // slice before it (or, in rows shorter than a slice, to none).  Each wave
+  // clears what it fetched itself, between its DMA wait and the barrier that
+  // every slice has anyway.  Clearing W is enough: the hidden chunks that meet
+  // the zeros are the same row's own, so an infinity or NaN in them has made
+  // the row's results NaN already.  (W and not the hidden states: an infinite
+  // weight must reach its own vocabulary entry only.)
+  auto clear_w_tail = [&](int stage) {
+#pragma unroll
+    for (int i = 0; i < kBlocksPerWave; ++i) {
+      const int c = dma_chunk(wave * kBlocksPerWave + i);
+      if (nk == 1 ? c >= row_chunks : c < nk * kChunks - row_chunks)
+        lds[stage * R::kStageSlots + (wave * kBlocksPerWave + i) * 64 + lane] = make_uint4(0, 0, 0, 0);
     }
   };
 
@@ -267,21 +299,21 @@ __global__ __launch_bounds__(kThreads, 1) void lmhead_logprob_kernel(LmheadArgs 
   const int frag_lane[kKSteps] = {(r16 * kChunks + ((0 + kchunk) ^ row_xor(r16))),
                                   (r16 * kChunks + ((4 + kchunk) ^ row_xor(r16)))};
   // the two W fragments (vocabulary blocks 2 pr, 2 pr + 1) of quarter pr of K-step ks
-  auto load_a = [&](int slice, int ks, int pr, uint4 (&dst)[2]) {
-    const uint4* base = &lds[slice % kStages][0][frag_lane[ks]];
+  auto load_a = [&](int stage, int ks, int pr, uint4 (&dst)[2]) {
+    const uint4* base = &lds[stage * R::kStageSlots + frag_lane[ks]];
 #pragma unroll
     for (int j = 0; j < 2; ++j) dst[j] = base[(wm * 128 + (2 * pr + j) * 16) * kChunks];
   };
   // hidden-state fragment of token block bn, K-step ks
-  auto load_b = [&](int slice, int ks, int bn, uint4& dst) {
-    dst = lds[slice % kStages][1][frag_lane[ks] + (wn * kWaveN + bn * 16) * kChunks];
+  auto load_b = [&](int stage, int ks, int bn, uint4& dst) {
+    dst = lds[stage * R::kStageSlots + kSlots + frag_lane[ks] + (wn * kWaveRows + bn * 16) * kChunks];
   };
-  // the 2 x kTB MFMAs of quarter pr
-  auto quarter_mfma = [&](const uint4 (&a)[2], const uint4 (&b)[kTB], int pr) {
+  // the 2 x TB MFMAs of quarter pr
+  auto quarter_mfma = [&](const uint4 (&a)[2], const uint4 (&b)[TB], int pr) {
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int i = 0; i < kTB; ++i) M::run(a[j], b[snake(j, i)], acc[2 * pr + j][snake(j, i)]);
+      for (int i = 0; i < TB; ++i) M::run(a[j], b[snake<TB>(j, i)], acc[2 * pr + j][snake<TB>(j, i)]);
   };
 
   // Online max / sum-of-exp update of one V-tile, then capture of the
@@ -289,10 +321,10 @@ __global__ __launch_bounds__(kThreads, 1) void lmhead_logprob_kernel(LmheadArgs 
   // the end of the vocabulary and rows >= V are excluded.
   auto epilogue = [&](int64_t vt, auto masked_tag) {
     constexpr bool kMasked = decltype(masked_tag)::value;
-    const int64_t vbase = vt * kTileV + wm * 128;   // first vocab row of this wave
+    const int64_t vbase = int64_t{vt} * kTileV + wm * 128;   // first vocab row of this wave
     const int64_t vlane = vbase + 4 * grp;          // + 16 bm + i: this lane's rows
 #pragma unroll
-    for (int bn = 0; bn < kTB; ++bn) {
+    for (int bn = 0; bn < TB; ++bn) {
       if (kMasked) {
 #pragma unroll
         for (int bm = 0; bm < kVB; ++bm)
@@ -348,12 +380,12 @@ __global__ __launch_bounds__(kThreads, 1) void lmhead_logprob_kernel(LmheadArgs 
 #pragma unroll
     for (int bm = 0; bm < kVB; ++bm)
 #pragma unroll
-      for (int bn = 0; bn < kTB; ++bn)
+      for (int bn = 0; bn < TB; ++bn)
 #pragma unroll
         for (int q = 0; q < 4; ++q) acc[bm][bn][q] = 0.f;
   };
 
-  // Gradient mode: G = g (1[v == y] - p) for the kVB x kTB blocks of this
+  // Gradient mode: G = g (1[v == y] - p) for the kVB x TB blocks of this
   // wave, rounded to bf16.  In each block a lane holds 4 consecutive
   // vocabulary entries of its token row: half of an 8-entry chunk (lane
   // groups 0 and 1 hold the two halves of one chunk, groups 2 and 3 those of
@@ -367,13 +399,17 @@ __global__ __launch_bounds__(kThreads, 1) void lmhead_logprob_kernel(LmheadArgs 
   // instruction covers four runs of 256 contiguous bytes (16 token rows x one
   // chunk each).  Rows >= V hold -inf, so p = 0 and G = 0 there, which
   // zero-fills the columns up to g_cols.
-  auto grad_epilogue = [&](int64_t vt) {
-    const int vbase = static_cast<int>(vt * kTileV) + wm * 128;   // V < 2^31
+  auto grad_epilogue = [&](int vt) {
+    const int vbase = vt * kTileV + wm * 128;   // V < 2^31
+    // G's address: uniform up to the pair of blocks, plus this byte offset
+    // (64-bit addresses per token column made the kernel spill); g_ld is at
+    // most one chunk's rows, so it stays far below 4 GiB
+    const uint32_t lane_off =
+        static_cast<uint32_t>(frag_chunk(grp) * p.g_ld + row0 + wn * kWaveRows + r16) * 16u;
 #pragma unroll
-    for (int bn = 0; bn < kTB; ++bn) {
-      const int64_t e = rt * kTileN + wn * kWaveN + bn * 16 + r16;
+    for (int bn = 0; bn < TB; ++bn) {
+      const int64_t e = row0 + wn * kWaveRows + bn * 16 + r16;
       const bool live = e < n_s;   // rows n_s .. round_up(n_s, 64) - 1 are written as zeros
-      uint16_t* gcol = p.g_out + e * 8;   // chunk c of this row: gcol + c * g_ld * 8
       const float gneg = -g_up[bn];
       // The sampled token's column gets g (1 - p), computed as g - g p (one
       // rounding); `code` is its place 4 bm + q among this lane's elements of
@@ -403,27 +439,27 @@ __global__ __launch_bounds__(kThreads, 1) void lmhead_logprob_kernel(LmheadArgs 
         // partner's second-block half (the lower half) and keep their own
         const auto s0 = __builtin_amdgcn_permlane16_swap(pk[0][0], pk[1][0], false, false);
         const auto s1 = __builtin_amdgcn_permlane16_swap(pk[0][1], pk[1][1], false, false);
-        const int chunk = (vbase + bp * 16) / 8 + frag_chunk(grp);
+        char* pair = reinterpret_cast<char*>(p.g_out) + static_cast<int64_t>((vbase + bp * 16) / 8) * p.g_ld * 16;
         // (the pair's 32 columns lie wholly below g_cols, a multiple of 64, or
         // wholly above).  Non-temporal: G is read back only by the two GEMMs,
         // long after it has left the L2, and these write-backs would
         // otherwise evict the tiles the next K-slices' DMAs read.
         if (e < n_s_pad && vbase + bp * 16 < p.g_cols)
           __builtin_nontemporal_store(u32x4_t{s0[0], s1[0], s0[1], s1[1]},
-                                      reinterpret_cast<u32x4_t*>(gcol + static_cast<int64_t>(chunk) * p.g_ld * 8));
+                                      reinterpret_cast<u32x4_t*>(pair + (lane_off + bn * 256)));
       }
     }
 #pragma unroll
     for (int bm = 0; bm < kVB; ++bm)
 #pragma unroll
-      for (int bn = 0; bn < kTB; ++bn)
+      for (int bn = 0; bn < TB; ++bn)
 #pragma unroll
         for (int q = 0; q < 4; ++q) acc[bm][bn][q] = 0.f;
   };
 
   // ---- pipelined main loop over (V-tile, K-slice) ------------------------
   // A K-slice is 2 K-steps x 4 quarters; quarter pr multiplies the W
-  // fragments of vocabulary blocks 2 pr, 2 pr + 1 with the kTB hidden-state
+  // fragments of vocabulary blocks 2 pr, 2 pr + 1 with the TB hidden-state
   // fragments.  Each quarter first reads what the next one needs: the next
   // quarter's two W fragments (alternating buffers fa[0], fa[1]) and, during
   // K-step 0, one hidden-state fragment of K-step 1 (fb[1]).  The slice's
@@ -431,89 +467,81 @@ __global__ __launch_bounds__(kThreads, 1) void lmhead_logprob_kernel(LmheadArgs 
   // reads the next slice's first W fragments and all of its K-step-0 hidden
   // fragments (fb[0]), and issues the DMA of the slice after next into the
   // stage just released, spread between its MFMAs.
-  const int n_pre = n_iter < kStages ? n_iter : kStages;
-  for (int sl = 0; sl < n_pre; ++sl) issue(sl);
-  wait_dma(n_pre - 1);
+  const int n_pre = n_iter < R::kStages ? n_iter : R::kStages;
+  for (int sl = 0; sl < n_pre; ++sl) {
+    next_issue();
+    set_issue();
+    unroll<R::kDma>(issue_one);
+  }
+  if (n_pre == R::kStages) wait_vmcnt<(R::kStages - 1) * R::kDma>();
+  else wait_vmcnt<0>();
+  if (n_pre < R::kStages) issue_stage = R::kStages - 1;   // (slot kStages takes stage 0)
+  if (KTAIL && nk == 1) clear_w_tail(0);
   raw_barrier();
-  if (k_tail && nk == 1) { clear_k_tail(0); raw_barrier(); }
 
-  uint4 fa[2][2], fb[2][kTB];
-  int it = 0;   // global slice counter
-  for (int64_t vt = vt0; vt < vt1; ++vt) {
-    load_a(it, 0, 0, fa[0]);
+  uint4 fa[2][2], fb[2][TB];
+  // One K-slice, in ring stage st.  next_tail: the slice after it is the last
+  // of its rows.
+  auto slice_step = [&](int st, bool next_tail) {
+    const int nst = next_stage(st);
+    // K-step 0
 #pragma unroll
-    for (int bn = 0; bn < kTB; ++bn) load_b(it, 0, bn, fb[0][bn]);
-    for (int kt = 0; kt < nk; ++kt, ++it) {
-      // K-step 0
+    for (int pr = 0; pr < 4; ++pr) {
+      if (pr < 3) load_a(st, 0, pr + 1, fa[(pr + 1) & 1]);
+      else load_a(st, 1, 0, fa[0]);
+      if (pr < TB) load_b(st, 1, pr, fb[1][pr]);
+      // keep the fragment reads for the next quarter ahead of this
+      // quarter's MFMAs, so their LDS latency hides under matrix work
+      __builtin_amdgcn_sched_barrier(0);
+      quarter_mfma(fa[pr & 1], fb[0], pr);
+    }
+    // K-step 1, quarters 0-2
 #pragma unroll
-      for (int pr = 0; pr < 4; ++pr) {
-        if (pr < 3) load_a(it, 0, pr + 1, fa[(pr + 1) & 1]);
-        else load_a(it, 1, 0, fa[0]);
-        load_b(it, 1, pr, fb[1][pr]);
-        // keep the fragment reads for the next quarter ahead of this
-        // quarter's MFMAs, so their LDS latency hides under matrix work
-        __builtin_amdgcn_sched_barrier(0);
-        quarter_mfma(fa[pr & 1], fb[0], pr);
-      }
-      // K-step 1, quarters 0-2
+    for (int pr = 0; pr < 3; ++pr) {
+      load_a(st, 1, pr + 1, fa[(pr + 1) & 1]);
+      if (pr == 0) next_issue();
+      __builtin_amdgcn_sched_barrier(0);
+      quarter_mfma(fa[pr & 1], fb[1], pr);
+    }
+    // K-step 1, quarter 3: the slice boundary.  Every read of this slice is
+    // issued: wait for the next slice, then recycle this slice's stage.  On
+    // the work item's last slice this waits for nothing and the reads of the
+    // "next slice" fetch stale (in-bounds, unused) LDS: keeping this path
+    // unconditional leaves no control-flow join before the MFMAs.  The DMAs
+    // of the slice kStages on are issued with this quarter's MFMAs.
+    wait_vmcnt<(R::kStages - 2) * R::kDma>();
+    if (KTAIL && next_tail) clear_w_tail(nst);
+    raw_barrier();
+    set_issue();
+    load_a(nst, 0, 0, fa[0]);
 #pragma unroll
-      for (int pr = 0; pr < 3; ++pr) {
-        load_a(it, 1, pr + 1, fa[(pr + 1) & 1]);
-        __builtin_amdgcn_sched_barrier(0);
-        quarter_mfma(fa[pr & 1], fb[1], pr);
-      }
-      // K-step 1, quarter 3: the slice boundary.  Every read of slice `it`
-      // is issued: wait for slice it+1, then recycle this slice's stage.  On
-      // the work item's last slice this waits for nothing and the reads of
-      // "slice it+1" fetch stale (in-bounds, unused) LDS: keeping this path
-      // unconditional leaves no control-flow join before the MFMAs.
-      if (KTAIL) {
-        const int after = n_iter - 2 - it;
-        wait_dma(after < kStages - 2 ? after : kStages - 2);
-        raw_barrier();
-        if (((it + 1) % nk) == nk - 1) { clear_k_tail(it + 1); raw_barrier(); }
-        if (it + kStages < n_iter) issue(it + kStages);
-        load_a(it + 1, 0, 0, fa[0]);
+    for (int bn = 0; bn < TB; ++bn) load_b(nst, 0, bn, fb[0][bn]);
+    __builtin_amdgcn_sched_barrier(0);
+    unroll<R::kDma>(issue_one);
+    quarter_mfma(fa[1], fb[1], 3);
+  };
+  int st = 0;   // ring stage of the current slice
+  for (int vt = vt0; vt < vt1; ++vt) {
+    load_a(st, 0, 0, fa[0]);
 #pragma unroll
-        for (int bn = 0; bn < kTB; ++bn) load_b(it + 1, 0, bn, fb[0][bn]);
-        __builtin_amdgcn_sched_barrier(0);
-        quarter_mfma(fa[1], fb[1], 3);
-      } else {
-        // As above, but the DMAs for slice it+kStages are spread between
-        // this quarter's MFMAs so their issue overlaps matrix work.  They are
-        // unconditional: past the end of the work item they fetch a copy of
-        // the last slice into the stage just freed, which nothing reads.
-        wait_dma(kStages - 2);
-        raw_barrier();
-        prep_issue(it + kStages, it + kStages < n_iter ? it + kStages : n_iter - 1);
-        load_a(it + 1, 0, 0, fa[0]);
-#pragma unroll
-        for (int bn = 0; bn < kTB; ++bn) load_b(it + 1, 0, bn, fb[0][bn]);
-        __builtin_amdgcn_sched_barrier(0);
-        constexpr int kM = 2 * kTB;                          // MFMAs per quarter
-        constexpr int kEvery = kM / kDmaPerSlice > 0 ? kM / kDmaPerSlice : 1;
-#pragma unroll
-        for (int j = 0; j < kM; ++j) {
-          M::run(fa[1][j / kTB], fb[1][snake(j / kTB, j % kTB)], acc[6 + j / kTB][snake(j / kTB, j % kTB)]);
-          if (j % kEvery == kEvery - 1 && j / kEvery < kDmaPerSlice) issue_one(j / kEvery, std::false_type{});
-        }
-#pragma unroll
-        for (int j = kM / kEvery; j < kDmaPerSlice; ++j) issue_one(j, std::false_type{});
-      }
+    for (int bn = 0; bn < TB; ++bn) load_b(st, 0, bn, fb[0][bn]);
+    for (int kt = 0; kt < nk; ++kt) {
+      slice_step(st, nk == 1 || kt == nk - 2);
+      st = next_stage(st);
     }
     if (GRAD) {
-      if ((vt + 1) * kTileV > V) {
+      if ((vt + int64_t{1}) * kTileV > V) {
         // rows >= V: -inf, so that they contribute G = 0
 #pragma unroll
         for (int bm = 0; bm < kVB; ++bm)
 #pragma unroll
-          for (int bn = 0; bn < kTB; ++bn)
+          for (int bn = 0; bn < TB; ++bn)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-              if (vt * kTileV + wm * 128 + bm * 16 + 4 * grp + q >= V) acc[bm][bn][q] = kNegInf;
+              if (int64_t{vt} * kTileV + wm * 128 + bm * 16 + 4 * grp + q >= V) acc[bm][bn][q] = kNegInf;
       }
       grad_epilogue(vt);
-    } else if ((vt + 1) * kTileV <= V) {
+    } else if ((vt + int64_t{1}) * kTileV <= V) {
       epilogue(vt, std::false_type{});
     } else {
       epilogue(vt, std::true_type{});
@@ -525,7 +553,7 @@ __global__ __launch_bounds__(kThreads, 1) void lmhead_logprob_kernel(LmheadArgs 
 
   // ---- merge the four lane groups, then the two vocabulary waves ----------
 #pragma unroll
-  for (int bn = 0; bn < kTB; ++bn) {
+  for (int bn = 0; bn < TB; ++bn) {
 #pragma unroll
     for (int x = 16; x <= 32; x <<= 1) {
       const float m2 = __shfl_xor(run_m[bn], x);
@@ -535,14 +563,14 @@ __global__ __launch_bounds__(kThreads, 1) void lmhead_logprob_kernel(LmheadArgs 
       combine(run_m[bn], run_s[bn], run_z[bn], run_t[bn], m2, s2, z2, t2);
     }
   }
-  float* xm = reinterpret_cast<float*>(&lds[0][0][0]);
-  float* xs = xm + kTileN;
-  float* xz = xs + kTileN;
-  float* xt = xz + kTileN;
+  float* xm = reinterpret_cast<float*>(lds);
+  float* xs = xm + R::kRowsN;
+  float* xz = xs + R::kRowsN;
+  float* xt = xz + R::kRowsN;
   if (wm == 1 && grp == 0) {
 #pragma unroll
-    for (int bn = 0; bn < kTB; ++bn) {
-      const int tcol = wn * kWaveN + bn * 16 + r16;
+    for (int bn = 0; bn < TB; ++bn) {
+      const int tcol = wn * kWaveRows + bn * 16 + r16;
       xm[tcol] = run_m[bn];
       xs[tcol] = run_s[bn];
       xz[tcol] = run_z[bn];
@@ -552,11 +580,11 @@ __global__ __launch_bounds__(kThreads, 1) void lmhead_logprob_kernel(LmheadArgs 
   __syncthreads();
   if (wm == 0 && grp == 0) {
 #pragma unroll
-    for (int bn = 0; bn < kTB; ++bn) {
-      const int tcol = wn * kWaveN + bn * 16 + r16;
+    for (int bn = 0; bn < TB; ++bn) {
+      const int tcol = wn * kWaveRows + bn * 16 + r16;
       float m = run_m[bn], s = run_s[bn], z = run_z[bn], t = run_t[bn];
       combine(m, s, z, t, xm[tcol], xs[tcol], xz[tcol], ENT ? xt[tcol] : 0.f);
-      const int64_t e = rt * kTileN + tcol;
+      const int64_t e = row0 + tcol;
       if (e < n_s) {
         const int64_t o = ch * p.part_stride + e;
         p.part_m[o] = m;
@@ -566,6 +594,26 @@ __global__ __launch_bounds__(kThreads, 1) void lmhead_logprob_kernel(LmheadArgs 
       }
     }
   }
+}
+
+template <bool BF16, bool KTAIL, int EPI>
+__global__ __launch_bounds__(kThreads, 1) void lmhead_logprob_kernel(LmheadArgs p) {
+  __shared__ uint4 lds[kLdsSlots];   // a ring of [W | hidden] stages, see Ring
+
+  // ---- work item: XCD-aware (row tile, vocabulary chunk), see plan.h -----
+  int64_t n_s = *p.n_scored - p.row_base;
+  n_s = n_s < 0 ? 0 : (n_s > p.row_cap ? p.row_cap : n_s);
+  const ItemGrid items = item_grid(n_s, p.n_ch);
+  int64_t rt, ch;
+  work_item(blockIdx.x, items, &rt, &ch);
+  if (rt >= items.n_rt) return;
+  // (the divisions run on the vector ALU: back to scalar registers)
+  ch = __builtin_amdgcn_readfirstlane(static_cast<int>(ch));
+  const int64_t row0 = __builtin_amdgcn_readfirstlane(static_cast<int>(rt * items.rows));
+  const int64_t left = __builtin_amdgcn_readfirstlane(static_cast<int>(n_s - row0 < items.rows ? n_s - row0 : items.rows));
+  if (left <= Ring<1>::kRowsN) run_item<BF16, KTAIL, EPI, 1>(p, row0, ch, n_s, lds);
+  else if (left <= Ring<2>::kRowsN) run_item<BF16, KTAIL, EPI, 2>(p, row0, ch, n_s, lds);
+  else run_item<BF16, KTAIL, EPI, 4>(p, row0, ch, n_s, lds);
 }
 
 // Combine the chunk partials of each scored row in a fixed order and write

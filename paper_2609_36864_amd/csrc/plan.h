@@ -18,6 +18,7 @@ constexpr int kTileN = 256;              // token rows per workgroup tile
 constexpr int kGroupRT = 4;              // row tiles per per-XCD launch group
 constexpr int kGroupCH = 32 / kGroupRT;  // vocabulary chunks per per-XCD launch group
 constexpr int kNumXcd = 8;               // XCDs per MI355X; workgroups go round-robin
+constexpr int kNumCu = 256;              // compute units
 constexpr int kCountBlockRows = 4096;    // rows per block of the compaction's count pass
 
 // How one call is cut up.  A call of n_rows rows runs in launches of at most
@@ -38,9 +39,10 @@ struct LmheadPlan {
   int planes;               // partial planes: max, sum of exp, sampled logit (+ entropy)
 };
 
-// The work items of one launch: row tiles x vocabulary chunks.
+// The work items of one launch: row tiles (of `rows` token rows) x vocabulary
+// chunks.
 struct ItemGrid {
-  int64_t n_rt, n_ch;
+  int64_t n_rt, n_ch, rows;
 };
 
 // Geometry of one launch over n <= plan.n_rows rows.
@@ -132,19 +134,35 @@ inline bool make_plan_bounded(int64_t n_rows_total, int64_t vocab, int64_t d, in
   return true;
 }
 
-// The work items of a launch that scores n_s rows.
+// The work items of a launch that scores n_s rows.  Tiles of kTileN rows, but
+//  - of half of that up to 3 / 2 kTileN rows, where a second whole tile would
+//    be mostly padding and W's stream from HBM, not the matrix work, sets the
+//    pace (V = 151,936, d = 2048: 300 rows 271 -> 246 us, 200 rows 224 -> 210;
+//    400 rows would go from 318 to 348);
+//  - of half or a quarter where there would be fewer items than CUs (more row
+//    tiles read W more often, but into CUs that would idle).
 __host__ __device__ inline ItemGrid item_grid(int64_t n_s, int64_t n_ch) {
-  return ItemGrid{ceil_div(n_s, kTileN), n_ch};
+  int64_t rows = n_s <= kTileN / 2 * 3 ? kTileN / 2 : kTileN;
+  while (rows > kTileN / 4 && ceil_div(n_s, rows) * n_ch < kNumCu) rows /= 2;
+  return ItemGrid{ceil_div(n_s, rows), n_ch, rows};
 }
 
 // Geometry of one launch over n rows (n <= plan.n_rows) with the call's
-// chunking.
+// chunking.  The grid has a workgroup for every item of any n_s <= n: whole
+// tiles, at most three half tiles, or, where those are fewer than kNumCu
+// items, narrower ones (at most four times as many).
 inline LmheadLaunch plan_launch(const LmheadPlan& p, int64_t n) {
   LmheadLaunch l{};
   l.n_grt = item_grid(n, p.n_ch);
   l.n_rt_max = l.n_grt.n_rt;
+  const int64_t halves = ceil_div(n, kTileN / 2);
+  int64_t tiles = ceil_div(n, kTileN);
+  if (tiles < (halves < 3 ? halves : 3)) tiles = halves < 3 ? halves : 3;
+  int64_t narrow = ceil_div(n, kTileN / 4) * p.n_ch;
+  if (narrow > 4 * kNumCu) narrow = 4 * kNumCu;
+  const int64_t items = tiles * p.n_ch > narrow ? tiles * p.n_ch : narrow;
   const int64_t round = kNumXcd * kGroupRT * kGroupCH;
-  l.grid = ceil_div(l.n_rt_max * p.n_ch, round) * round;
+  l.grid = ceil_div(items, round) * round;
   return l;
 }
 

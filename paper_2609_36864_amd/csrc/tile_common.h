@@ -5,6 +5,8 @@
 // step for bf16 and fp32 operands.  Not part of the public ABI.
 #pragma once
 
+#include <utility>
+
 #include "hdl_internal.h"
 
 namespace hdl {
@@ -36,6 +38,16 @@ static_assert(2 * 16 * kVB == kTileV && 4 * kWaveN == kTileN, "8 waves as 2 (M) 
 static_assert(kStages * 2 * kSlots * 16 <= 160 * 1024, "LDS ring exceeds 160 KB");
 static_assert(kDmaPerSlice * (kStages - 1) <= 63, "vmcnt range");
 
+// f(0), f(1), .. f(N - 1), each argument a compile-time constant.
+template <class F, int... I>
+__device__ __forceinline__ void unroll_seq(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void unroll(F&& f) {
+  unroll_seq(f, std::make_integer_sequence<int, N>{});
+}
+
 // XOR pattern of a row of 128 bytes: 8 consecutive rows get 8 distinct
 // chunks, and rows r and r + 8 differ too, so a fragment read (16 rows; see
 // frag_chunk) touches every bank at most once per pass.
@@ -64,6 +76,13 @@ __device__ __forceinline__ void dma16(uint64_t sbase, uint32_t voff, uint32_t ld
       : "=&s"(saved)
       : "s"(lds_base), "v"(voff), "s"(sbase)
       : "memory");
+}
+
+// A wave-uniform value, in scalar registers.
+__device__ __forceinline__ uint64_t uniform64(uint64_t x) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(x));
+  const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(x >> 32));
+  return (static_cast<uint64_t>(hi) << 32) | lo;
 }
 
 // Wait until at most N of this lane's memory loads (DMAs) are outstanding.
@@ -113,14 +132,15 @@ template <> struct Mma16<false> {
   }
 };
 
-// Order of the MFMAs of a quarter (two A fragments j = 0, 1 times kTB B
+// Order of the MFMAs of a quarter (two A fragments j = 0, 1 times TB B
 // fragments): B fragment snake(j, i) is the i-th for A fragment j, i.e.
-// 0 .. kTB-1 for the first and kTB-1 .. 0 for the second, so that the B
+// 0 .. TB-1 for the first and TB-1 .. 0 for the second, so that the B
 // operand is the same on both sides of the change of A and fewer operand
 // bits switch between consecutive MFMAs (with random data the matrix pipes
 // then sustain about 2 % more under the power limit).  The accumulator
 // blocks are independent, so the order does not change any result.
-__device__ __forceinline__ constexpr int snake(int j, int i) { return (j & 1) ? kTB - 1 - i : i; }
+template <int TB = kTB>
+__device__ __forceinline__ constexpr int snake(int j, int i) { return (j & 1) ? TB - 1 - i : i; }
 
 // Which of a K-step's four 16-byte chunks lane group g reads: (0, 2, 1, 3).
 // A ds_read_b128 serves lanes i..i+7 together with lanes i+32..i+39, i.e.

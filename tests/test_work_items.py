@@ -23,6 +23,7 @@ def checker(tmp_path_factory):
 # one row; less than a tile; a tile and a remainder; several groups of row
 # tiles with 1, 2 and 3 left; many chunks, few, one; a large launch
 @pytest.mark.parametrize("n_rows,vocab,d", [(1, 1, 8), (1, 151936, 2048), (96, 151936, 2048), (300, 4096, 256),
+                                            (384, 151936, 2048), (513, 151936, 2048), (700, 21000, 64),
                                             (1554, 151936, 4096), (3333, 50257, 1000), (9 * 256, 9000, 64),
                                             (65024, 151936, 2048)])
 def test_every_item_once_and_shared_tiles(checker, n_rows, vocab, d):
