@@ -74,6 +74,47 @@ __device__ __forceinline__ void combine(float& m, float& s, float& z, float& t, 
   z = fmaxf(z, z2);
 }
 
+// Eight fp32 values as sums of three bf16 values each: the value rounded to
+// bf16, the rest rounded to bf16, and what is left, which has at most 8
+// significant bits (8 + 8 + 8 with signed rests cover the 24 of an fp32; both
+// subtractions are exact).  Exact but for pieces below bf16's smallest
+// denormal, 2^-133, which are lost; under kSplitMax on the other side that is
+// less than 2^-73 of a logit.  An infinity has no such pieces; a NaN stays NaN.
+struct Split3 {
+  bf16x8_t p[3];
+};
+constexpr float kSplitMax = 0x1p60f;
+
+__device__ __forceinline__ Split3 split3(const uint4 (&x)[2]) {
+  uint32_t u[3][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint4& q = x[i / 2];
+    f32x2_t v = {__uint_as_float(i % 2 ? q.z : q.x), __uint_as_float(i % 2 ? q.w : q.y)};
+#pragma unroll
+    for (int o = 0; o < 3; ++o) {
+      u[o][i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
+      v[0] -= __uint_as_float(u[o][i] << 16);
+      v[1] -= __uint_as_float(u[o][i] & 0xffff0000u);
+    }
+  }
+  Split3 s;
+#pragma unroll
+  for (int o = 0; o < 3; ++o) s.p[o] = __builtin_bit_cast(bf16x8_t, make_uint4(u[o][0], u[o][1], u[o][2], u[o][3]));
+  return s;
+}
+
+// The largest |x| of the eight values and m (quiet NaNs are passed over).
+// (v_max3_f32 itself: fmaxf would first canonicalise every operand)
+__device__ __forceinline__ float max_abs(const uint4 (&x)[2], float m) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(x[i].x), "v"(x[i].y));
+    asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(x[i].z), "v"(x[i].w));
+  }
+  return m;
+}
+
 static_assert(kKSteps == 2, "a K-slice is two K-steps");
 static_assert(kVB % 2 == 0, "the gradient epilogue pairs vocabulary blocks");
 
@@ -125,7 +166,6 @@ template <bool BF16, bool KTAIL, int EPI, int TB>
 __device__ __forceinline__ void run_item(const LmheadArgs& p, int64_t row0, int64_t ch, int64_t n_s, uint4* lds) {
   constexpr bool ENT = EPI == kEpiEntropy;
   constexpr bool GRAD = EPI == kEpiGrad;
-  using M = Mma16<BF16>;
   using R = Ring<TB>;
   constexpr int kEsz = BF16 ? 2 : 4;
   constexpr int kElemsPer16B = 16 / kEsz;
@@ -313,7 +353,7 @@ __device__ __forceinline__ void run_item(const LmheadArgs& p, int64_t row0, int6
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int i = 0; i < TB; ++i) M::run(a[j], b[snake<TB>(j, i)], acc[2 * pr + j][snake<TB>(j, i)]);
+      for (int i = 0; i < TB; ++i) Mma16<true>::run(a[j], b[snake<TB>(j, i)], acc[2 * pr + j][snake<TB>(j, i)]);
   };
 
   // Online max / sum-of-exp update of one V-tile, then capture of the
@@ -482,7 +522,7 @@ __device__ __forceinline__ void run_item(const LmheadArgs& p, int64_t row0, int6
   uint4 fa[2][2], fb[2][TB];
   // One K-slice, in ring stage st.  next_tail: the slice after it is the last
   // of its rows.
-  auto slice_step = [&](int st, bool next_tail) {
+  [[maybe_unused]] auto slice_bf16 = [&](int st, bool next_tail) {
     const int nst = next_stage(st);
     // K-step 0
 #pragma unroll
@@ -520,11 +560,88 @@ __device__ __forceinline__ void run_item(const LmheadArgs& p, int64_t row0, int6
     unroll<R::kDma>(issue_one);
     quarter_mfma(fa[1], fb[1], 3);
   };
+  // One K-slice of fp32 operands.  v_mfma_f32_16x16x4_f32 does 157 TFLOP/s on
+  // the whole chip, the bf16 form 16 times that, and an fp32 value is the sum
+  // of three bf16 values exactly (split3); so each pair of 16-row fragments is
+  // multiplied as the six products of pieces whose orders add up to at most 2
+  // (what is left out is below 2^-26 of |w h|, under the rounding of the fp32
+  // sums), the smallest first.  A slice's 32 K values are one K-step of the
+  // bf16 MFMA: lane group g holds the chunks frag_chunk(g) and
+  // 4 + frag_chunk(g) of W and hidden rows alike.  Pieces are made in
+  // registers, where 6 VALU instructions per value run beside the other
+  // wave's MFMAs, so HBM and LDS traffic stay those of fp32.  Fragments with
+  // a value too large for the split (kSplitMax; an infinite weight would meet
+  // the zero pieces of the hidden states) are multiplied by the fp32 MFMA.
+  // 2,048 rows, d 1024, V 32,000: 955 -> 682 us (140 -> 197 TFLOP/s of fp32
+  // products, 1.18 PFLOP/s of bf16 ones), distance to the 64-bit result
+  // 6.1e-8 -> 5.7e-8.  Splitting a block between the MFMAs of the one before
+  // it, which 12 more registers allow with a few spills, took 696 us.
+  [[maybe_unused]] auto slice_f32 = [&](int st, bool next_tail) {
+    const int nst = next_stage(st);
+    const uint4* abase = &lds[st * R::kStageSlots + wm * 128 * kChunks];
+    const uint4* bbase = &lds[st * R::kStageSlots + kSlots + wn * kWaveRows * kChunks];
+    auto load2 = [&](const uint4* base, int block, uint4 (&dst)[2]) {
+      dst[0] = base[block * 16 * kChunks + frag_lane[0]];
+      dst[1] = base[block * 16 * kChunks + frag_lane[1]];
+    };
+    Split3 sb[TB];
+    float bmax = 0.f;
+    uint4 ra[2];
+    {
+      uint4 rb[TB][2];
+#pragma unroll
+      for (int bn = 0; bn < TB; ++bn) load2(bbase, bn, rb[bn]);
+      load2(abase, 0, ra);
+      next_issue();
+#pragma unroll
+      for (int bn = 0; bn < TB; ++bn) {
+        bmax = max_abs(rb[bn], bmax);
+        sb[bn] = split3(rb[bn]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+#pragma unroll
+    for (int bm = 0; bm < kVB; ++bm) {
+      if (__builtin_expect(__any(max_abs(ra, bmax) >= kSplitMax), 0)) {
+#pragma unroll
+        for (int bn = 0; bn < TB; ++bn) {
+          uint4 rb[2];
+          load2(bbase, bn, rb);
+          Mma16<false>::run(ra[0], rb[0], acc[bm][bn]);
+          Mma16<false>::run(ra[1], rb[1], acc[bm][bn]);
+        }
+        if (bm + 1 < kVB) load2(abase, bm + 1, ra);
+      } else {
+        const Split3 sa = split3(ra);
+        if (bm + 1 < kVB) load2(abase, bm + 1, ra);
+        __builtin_amdgcn_sched_barrier(0);
+        // (the TB accumulators in turn: consecutive MFMAs are independent)
+#pragma unroll
+        for (int o = 0; o < 6; ++o) {
+          constexpr int kA[6] = {1, 2, 0, 1, 0, 0}, kB[6] = {1, 0, 2, 0, 1, 0};
+#pragma unroll
+          for (int bn = 0; bn < TB; ++bn)
+            acc[bm][bn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sa.p[kA[o]], sb[bn].p[kB[o]], acc[bm][bn], 0, 0, 0);
+        }
+      }
+    }
+    wait_vmcnt<(R::kStages - 2) * R::kDma>();
+    if (KTAIL && next_tail) clear_w_tail(nst);
+    raw_barrier();
+    set_issue();
+    unroll<R::kDma>(issue_one);
+  };
+  auto slice_step = [&](int st, bool next_tail) {
+    if constexpr (BF16) slice_bf16(st, next_tail);
+    else slice_f32(st, next_tail);
+  };
   int st = 0;   // ring stage of the current slice
   for (int vt = vt0; vt < vt1; ++vt) {
-    load_a(st, 0, 0, fa[0]);
+    if constexpr (BF16) {
+      load_a(st, 0, 0, fa[0]);
 #pragma unroll
-    for (int bn = 0; bn < TB; ++bn) load_b(st, 0, bn, fb[0][bn]);
+      for (int bn = 0; bn < TB; ++bn) load_b(st, 0, bn, fb[0][bn]);
+    }
     for (int kt = 0; kt < nk; ++kt) {
       slice_step(st, nk == 1 || kt == nk - 2);
       st = next_stage(st);

@@ -104,8 +104,8 @@ __device__ __forceinline__ void raw_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// The MFMA shape of the tile kernels: v_mfma_f32_16x16x32_bf16 (fp32
-// inputs: four v_mfma_f32_16x16x4_f32 over one 16-byte fragment).  A
+// The MFMA shape of the tile kernels: v_mfma_f32_16x16x32_bf16 (Mma16<false>:
+// four v_mfma_f32_16x16x4_f32 over one 16-byte fragment of fp32).  A
 // fragment is 16 rows (M or N indices) of one operand: lane l holds row
 // (l mod 16) and 16 bytes of consecutive K values, which lane group
 // g = l div 16 takes from 16-byte chunk 4 ks + frag_chunk(g) of K-step ks.
