@@ -401,13 +401,25 @@ BwdPlan make_bwd_plan(int64_t n_rows, int64_t vocab, int64_t d) {
                                 : kBwdChunkRows;
   p.v_pad = static_cast<int64_t>(round_up(static_cast<size_t>(vocab), 64));
   p.n_chunks = (n_rows + p.nc - 1) / p.nc;
-  // dH = G W has nc/256 x d/256 output tiles; split the vocabulary so that
-  // about 512 workgroups run.
+  // dH = G W has nc/256 x d/256 output tiles, each a sum over the whole
+  // vocabulary; it is split so that the CUs, one workgroup each, run out of
+  // work together.  A round of workgroups costs its K-slices and, per split,
+  // about 40 slices' time of pipeline fill and of partial sums written and read
+  // back.  Whole calls at the chosen split against 8 (the most there were):
+  // 300 rows, d 2048, V 151,936: 16 splits 928 us, 8 (128 workgroups) 1122;
+  // 700 rows: 10 splits (240) 1448, 11 (264) 1686, 8 1509; 3,000 rows, d 1024,
+  // V 32,000: 5 (240) 556, 6 (288) 657, 8 (384) 611; 5,000 rows, d 2048,
+  // V 151,936: 3 (480) 7697, 4 (640) 8117.
   const int64_t tiles = (p.nc / hdl::kTileN) * ((d + hdl::kTileN - 1) / hdl::kTileN);
-  int64_t s = (512 + tiles - 1) / tiles;
-  s = s < 1 ? 1 : (s > 8 ? 8 : s);
   const int64_t slices = p.v_pad / 64;
-  if (s > slices) s = slices;
+  int64_t s = 1, best = 0;
+  for (int64_t c = 1; c <= 64 && c <= slices; ++c) {
+    const int64_t cost = hdl::ceil_div(tiles * c, hdl::kNumCu) * (hdl::ceil_div(slices, c) + 40);
+    if (c == 1 || cost < best) {
+      s = c;
+      best = cost;
+    }
+  }
   p.k_split = (slices + s - 1) / s * 64;
   p.splits = (p.v_pad + p.k_split - 1) / p.k_split;
   p.fwd = hdl::make_plan(p.nc, vocab, d, 2);
@@ -452,6 +464,7 @@ hdl::GemmArgs gemm_args(const void* a, int64_t lda, int a_layout, int64_t a_cols
   g.tiles_n = (n + hdl::kTileN - 1) / hdl::kTileN;
   g.gn = g.tiles_n < 4 ? g.tiles_n : 4;
   g.gm = 32 / g.gn;
+  if (g.gm > g.tiles_m) g.gm = g.tiles_m;
   g.c = c;
   g.ldc = ldc;
   return g;

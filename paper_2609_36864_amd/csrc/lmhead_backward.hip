@@ -220,27 +220,16 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_kernel(GemmArgs p) {
   const int grp = lane >> 4;
 
   // ---- work item: XCD-aware (m-tile, n-tile, split) ----------------------
-  // The j-th workgroup of an XCD belongs to launch group j / 32 of that XCD;
-  // a group is gm x gn tiles of one split, sharing A and B rows through L2.
-  // Consecutive groups (which run at the same time on neighbouring XCDs)
-  // take the n-groups of one m-group first, so the XCDs that read the same
-  // rows of A (the large logit gradient) read them together and all but the
-  // first find them in the memory-side cache (3.7 % faster at c2 than
-  // m-groups first).
-  const int64_t b = blockIdx.x;
-  const int64_t xcd = b % kNumXcd;
-  const int64_t j = b / kNumXcd;
-  const int64_t grp_id = (j / (p.gm * p.gn)) * kNumXcd + xcd;
-  const int64_t loc = j % (p.gm * p.gn);
-  const int64_t n_gm = (p.tiles_m + p.gm - 1) / p.gm;
-  const int64_t n_gn = (p.tiles_n + p.gn - 1) / p.gn;
+  // Workgroups go to the XCDs round-robin; run r of 32 items is the next 32
+  // workgroups of XCD r mod 8, so every XCD gets an equal share (gemm_item).
+  int64_t tm, tn, split;
+  const int64_t j = blockIdx.x / kNumXcd;
+  if (!gemm_item(((j / 32) * kNumXcd + blockIdx.x % kNumXcd) * 32 + j % 32, p, &tm, &tn, &split)) return;
   // (the runtime divisions run on the vector ALU; readfirstlane puts the
   // wave-uniform results back in scalar registers for the DMA base)
-  const int64_t split = __builtin_amdgcn_readfirstlane(static_cast<int>(grp_id / (n_gm * n_gn)));
-  const int64_t rem = grp_id % (n_gm * n_gn);
-  const int64_t tm = __builtin_amdgcn_readfirstlane(static_cast<int>((rem / n_gn) * p.gm + loc % p.gm));
-  const int64_t tn = __builtin_amdgcn_readfirstlane(static_cast<int>((rem % n_gn) * p.gn + loc / p.gm));
-  if (split >= p.splits || tm >= p.tiles_m || tn >= p.tiles_n) return;
+  split = __builtin_amdgcn_readfirstlane(static_cast<int>(split));
+  tm = __builtin_amdgcn_readfirstlane(static_cast<int>(tm));
+  tn = __builtin_amdgcn_readfirstlane(static_cast<int>(tn));
 
   int64_t m_valid = p.m, k_valid = p.k;
   if (p.dyn_dim != 0) {
@@ -304,7 +293,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_kernel(GemmArgs p) {
 #pragma unroll
       for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
-        for (int i = 0; i < kTB; ++i) M::run(fa_[jj], fb_[snake(jj, i)], acc[2 * pr + jj][snake(jj, i)]);
+        for (int i = 0; i < kTB; ++i) M::run(fb_[snake(jj, i)], fa_[jj], acc[2 * pr + jj][snake(jj, i)]);
     };
 
     const int n_pre = n_iter < kStages ? n_iter : kStages;
@@ -355,30 +344,31 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_kernel(GemmArgs p) {
       static_assert(kM == kDmaPerSlice, "one DMA per MFMA of the last quarter");
 #pragma unroll
       for (int q = 0; q < kM; ++q) {
-        M::run(fa[1][q / kTB], fb[1][snake(q / kTB, q % kTB)], acc[6 + q / kTB][snake(q / kTB, q % kTB)]);
+        M::run(fb[1][snake(q / kTB, q % kTB)], fa[1][q / kTB], acc[6 + q / kTB][snake(q / kTB, q % kTB)]);
         issue_one(q);
       }
     }
     wait_vmcnt<0>();
   }
 
-  // ---- store: in each block, lane l holds column l mod 16 of rows
-  // 4 (l div 16) + q, so one store instruction covers 4 rows x 64 bytes ----
+  // ---- store: B fragments are the MFMA's A operand, so in each block lane l
+  // holds row l mod 16 (M), columns 4 (l div 16) + 0..3 (N): 16-byte stores,
+  // and the four blocks of a row fill whole 128-byte lines one after the
+  // other (dW of 300 rows, d 2048, V 151,936, which is little but its 1.24 GB
+  // of stores: 505 -> 437 us against 4-byte stores, column blocks outermost)
   float* cbase = p.c + split * p.c_split_stride;
 #pragma unroll
-  for (int bn = 0; bn < kTB; ++bn) {
-    const int64_t n = tn * kTileN + wn * kWaveN + bn * 16 + r16;
-    if (n >= p.n) continue;
+  for (int bm = 0; bm < kVB; ++bm) {
+    const int64_t m = tm * kTileV + wm * 16 * kVB + bm * 16 + r16;
+    if (m >= m_valid) continue;
+    float* row = cbase + m * p.ldc;
 #pragma unroll
-    for (int bm = 0; bm < kVB; ++bm)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int64_t m = tm * kTileV + wm * 16 * kVB + bm * 16 + 4 * grp + q;
-        if (m < m_valid) {
-          float* dst = cbase + m * p.ldc + n;
-          *dst = p.beta ? *dst + acc[bm][bn][q] : acc[bm][bn][q];
-        }
-      }
+    for (int bn = 0; bn < kTB; ++bn) {
+      const int64_t n = tn * kTileN + wn * kWaveN + bn * 16 + 4 * grp;
+      if (n >= p.n) continue;   // (n and ldc are multiples of 4)
+      f32x4_t* dst = reinterpret_cast<f32x4_t*>(row + n);
+      *dst = p.beta ? *dst + acc[bm][bn] : acc[bm][bn];
+    }
   }
 }
 
@@ -450,9 +440,8 @@ __global__ __launch_bounds__(256) void zero_masked_rows_kernel(const uint8_t* __
 }  // namespace
 
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t stream) {
-  const int64_t per_group = a.gm * a.gn;
-  const int64_t groups = ((a.tiles_m + a.gm - 1) / a.gm) * ((a.tiles_n + a.gn - 1) / a.gn) * a.splits;
-  const int64_t grid = (groups + kNumXcd - 1) / kNumXcd * kNumXcd * per_group;
+  const int64_t round = kNumXcd * 32;
+  const int64_t grid = (a.tiles_m * a.tiles_n * a.splits + round - 1) / round * round;
   if (grid <= 0) return hipSuccess;
   const dim3 g(static_cast<unsigned>(grid)), blk(kThreads);
   if (a.a_layout == kLayoutCmRow && a.b_layout == kLayoutKRow)
