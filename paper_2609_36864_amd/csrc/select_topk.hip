@@ -8,17 +8,28 @@
 //     s     = |delta|,  eligible = mask[t] != 0 and delta finite.
 // (In value mode, s is the value itself.)  Scores map to 32-bit keys that
 // order like the floats (sign-magnitude flipped to an unsigned order, -0
-// folded onto +0).  The k largest s are found by a radix select on the
-// keys: four 8-bit digits, most significant first, each resolved from an LDS
-// histogram (the first one built while the keys are staged) by one wave.
-// That yields the threshold score S and how many positions at exactly S are
-// needed.  Each wave then sweeps a contiguous range of positions, its lanes
-// on consecutive positions (coalesced, and spread over the LDS banks), and
-// takes every score above S and, when only some of the positions at S are
-// needed, the lowest-indexed ones (the ties of lower wave ranges are counted
-// first).  The kk <= 1024 winners are sorted by the composite key (s, ~t)
-// with a bitonic network -- in one wave's registers for kk <= 64, else in
-// LDS -- giving the order (s descending, t ascending).
+// folded onto +0).  Every thread keeps the largest key of the positions it
+// reads; the kk-th largest of those 1024 keys belongs to kk different
+// positions, so no winner lies below it, and few other positions lie above
+// (about 1024 ln(1024 / (1024 - kk)) in all where scores are in no particular
+// order).  One sweep collects the positions from that bound up, and ordering
+// them by the composite key (s, ~t) leaves the kk winners first: (s
+// descending, t ascending).
+//
+// Where far more positions reach the bound (equal scores) or kk is large, the
+// kk-th largest s is found by a radix select on the keys instead: four 8-bit
+// digits, most significant first, each resolved from an LDS histogram by one
+// wave.  That yields the threshold score S and how many
+// positions at exactly S are needed.  Each wave then sweeps a contiguous range
+// of positions, its lanes on consecutive positions (coalesced, and spread over
+// the LDS banks), and takes every score above S and, when only some of the
+// positions at S are needed, the lowest-indexed ones (the ties of lower wave
+// ranges are counted first).
+//
+// Bound by latency: one root is one CU's work.  Scores share a few exponents,
+// so the radix select's histogram adds, which it had to make for every
+// position, mostly met in one LDS word: 4 roots of 32,768 positions, k 32,
+// 36.6 us; collecting above the bound 18.
 //
 // Branch-point constraints (the paper applies the same ones to every
 // localization method, Sec. 4.3): candidates may be restricted to a per-root
@@ -41,6 +52,13 @@ constexpr int kWaves = kThreads / 64;
 // after the first pass (128 KB), so the radix passes and the collect pass
 // do not re-read global memory; longer roots recompute them each pass.
 constexpr int kStageMax = 32768;
+// Up to this many ranked positions the candidates are cut by the threads'
+// maxima; up to kCutMaxLong on long roots, where a sweep costs more than
+// ordering the 710 or so candidates left for 512 (k 512: 64 roots of 20,000
+// 39 -> 31 us, but 256 roots of 4,096 22.7 -> 24.2).
+constexpr int kCutMax = 128;
+constexpr int kCutMaxLong = 512;
+constexpr int kCutLong = 16384;
 
 struct Scratch {
   int welig[kWaves];    // candidates per wave
@@ -51,6 +69,8 @@ struct Scratch {
   int n_thr;            // candidates scoring exactly the threshold
   int n_taken;          // winner slots handed out so far
   unsigned long long keys[kThreads];
+  unsigned tmax[kThreads];   // each thread's largest candidate key
+  unsigned bound;
   int kept;
   unsigned staged[kStageMax];   // candidate key per position, 0 = not a candidate
 };
@@ -65,6 +85,20 @@ __device__ __forceinline__ int wave_sum(int v) {
 __device__ __forceinline__ int lanes_below(unsigned long long m) {
   return __builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(m >> 32),
                                    __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(m), 0u));
+}
+
+// One more key in `bin` of an LDS histogram for every lane that is on, where
+// many keys are equal: adds to one LDS word go one after the other, so the lanes
+// of the first lane's bin add together (4 roots of 32,768 equal scores 138 ->
+// 59 us; on scores in no particular order it costs 10 %).
+__device__ __forceinline__ void hist_add(int* hist, bool on, unsigned bin) {
+  const unsigned long long m = __ballot(on);
+  if (m == 0ull) return;
+  const int leader = __builtin_ctzll(m);
+  const unsigned first = static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(bin), leader));
+  const unsigned long long same = __ballot(on && bin == first);
+  if (static_cast<int>(threadIdx.x & 63) == leader) atomicAdd(&hist[first], __popcll(same));
+  else if (on && bin != first) atomicAdd(&hist[bin], 1);
 }
 
 struct Pos {
@@ -144,9 +178,10 @@ __global__ __launch_bounds__(kThreads) void select_kernel(const float* __restric
   const int64_t t_hi = r_hi ? r_hi[r] : T - 1;
 
   // ---- eligibility count (and the optional signed delta) -----------------
-  // A staged root also gets the histogram of its keys' top digit here, the
-  // first radix pass's, so that pass needs no sweep of its own.
   const bool staged = T <= kStageMax;
+  // Only a large pool goes straight to the radix select: its first digit's
+  // histogram is then built here, so that digit needs no sweep of its own.
+  const bool cut = pool <= (T >= kCutLong ? kCutMaxLong : kCutMax);
   for (int i = tid; i < 2 * 256; i += kThreads) (&sh.hist[0][0])[i] = 0;
   if (tid == 0) sh.n_taken = 0;
   __syncthreads();
@@ -155,6 +190,7 @@ __global__ __launch_bounds__(kThreads) void select_kernel(const float* __restric
   // overlap.
   constexpr int kBatch = 8;
   int c = 0;
+  unsigned best = 0;   // largest candidate key of this thread
   auto first_pass = [&](auto has_mask) {
     constexpr bool kMask = decltype(has_mask)::value;
     for (int64_t t0 = tid; t0 < T; t0 += kBatch * kThreads) {
@@ -175,10 +211,12 @@ __global__ __launch_bounds__(kThreads) void select_kernel(const float* __restric
           const Pos p = make_pos<VALUES>(a[j], b[j], mk[j] != 0);
           if (delta_out) delta_out[base + t] = p.delta;
           const bool cand = p.elig && t >= t_lo && t <= t_hi;
+          const unsigned key = cand ? p.key : 0u;
           if (staged) {
-            sh.staged[t] = cand ? p.key : 0u;
-            if (cand) atomicAdd(&sh.hist[0][p.key >> 24], 1);
+            sh.staged[t] = key;
+            if (!cut && cand) atomicAdd(&sh.hist[0][key >> 24], 1);
           }
+          best = best > key ? best : key;
           c += cand ? 1 : 0;
         }
       }
@@ -188,13 +226,76 @@ __global__ __launch_bounds__(kThreads) void select_kernel(const float* __restric
   else first_pass(std::false_type{});
   c = wave_sum(c);
   if (lane == 0) sh.welig[wave] = c;
+  sh.tmax[tid] = best;
   __syncthreads();   // (also publishes the staged keys and the first histogram)
   int n_elig = 0;
 #pragma unroll
   for (int i = 0; i < kWaves; ++i) n_elig += sh.welig[i];
   const int kk = n_elig < pool ? n_elig : pool;
 
-  if (kk > 0) {
+  const int64_t per_w = ((T + kWaves - 1) / kWaves + 63) / 64 * 64;
+  const int64_t w_beg = wave * per_w;
+  const int64_t w_end = w_beg + per_w < T ? w_beg + per_w : T;
+  // Slots for the lanes that take a position t with this key; tk: their mask.
+  auto put = [&](unsigned long long tk, bool take, unsigned key, int64_t t) {
+    int slot0 = 0;
+    if (lane == 0) slot0 = atomicAdd(&sh.n_taken, __popcll(tk));
+    slot0 = __shfl(slot0, 0);
+    if (take) {
+      const int slot = slot0 + lanes_below(tk);
+      if (slot < kThreads)
+        sh.keys[slot] = (static_cast<unsigned long long>(key) << 32) |
+                        static_cast<unsigned long long>(0xFFFFFFFFu - static_cast<unsigned>(t));
+    }
+  };
+
+  int n_keys = 0;   // composite keys in sh.keys, the kk winners among them
+  if (cut && kk > 0) {
+    // ---- the bound: the kk-th largest of the threads' maxima, rounded down
+    // to its upper 16 bits (0 where fewer threads have a candidate) ----------
+    if (wave == 0) {
+      unsigned v[kThreads / 64];
+#pragma unroll
+      for (int i = 0; i < kThreads / 64; ++i) v[i] = sh.tmax[i * 64 + lane];
+      auto reach = [&](unsigned x) {
+        int n = 0;
+#pragma unroll
+        for (int i = 0; i < kThreads / 64; ++i) n += __popcll(__ballot(v[i] >= x));
+        return n;
+      };
+      unsigned bound = 0;
+      for (int bit = 31; bit >= 16; --bit)
+        if (reach(bound | (1u << bit)) >= kk) bound |= 1u << bit;
+      bound = bound > 0u ? bound : 1u;
+      // far more maxima than kk at the bound are ties: nothing to gain
+      const bool ties = reach(bound) > 2 * kk + 128;
+      if (lane == 0) sh.bound = ties ? 0u : bound;
+    }
+    __syncthreads();
+    const unsigned bound = sh.bound;
+    for (int64_t t0 = bound > 0u ? w_beg : w_end; t0 < w_end; t0 += 64 * kBatch) {
+      unsigned key[kBatch];
+#pragma unroll
+      for (int j = 0; j < kBatch; ++j) {
+        const int64_t t = t0 + j * 64 + lane;
+        key[j] = t < w_end ? cand_key<VALUES>(sh, staged, lo, lh, mask, base, t, t_lo, t_hi) : 0u;
+      }
+#pragma unroll
+      for (int j = 0; j < kBatch; ++j) {
+        const unsigned long long tk = __ballot(key[j] >= bound);
+        if (tk != 0ull) put(tk, key[j] >= bound, key[j], t0 + j * 64 + lane);
+      }
+    }
+    __syncthreads();
+    n_keys = sh.n_taken;
+    if (n_keys > kThreads) {   // too many: the radix select finds the exact threshold
+      __syncthreads();
+      if (tid == 0) sh.n_taken = 0;
+      n_keys = 0;
+    }
+  }
+
+  if (kk > 0 && n_keys == 0) {
     // ---- radix select of the kk-th largest score --------------------------
     // Per digit: one sweep adds the positions that match the prefix so far
     // to this digit's histogram (and clears the other one for the next
@@ -206,19 +307,27 @@ __global__ __launch_bounds__(kThreads) void select_kernel(const float* __restric
     for (int dg = 0; dg < 4; ++dg) {
       const int shift = 24 - 8 * dg;
       int* hist = sh.hist[dg & 1];
-      if (dg > 0 || !staged) {
+      if (dg > 0 || !staged || cut) {
         if (dg > 0 && tid < 256) sh.hist[(dg + 1) & 1][tid] = 0;
-        for (int64_t t0 = tid; t0 < T; t0 += kBatch * kThreads) {
-          unsigned key[kBatch];
+        auto sweep = [&](auto ties) {   // (ties: the cut gave up on this root)
+          for (int64_t t0 = tid; t0 < T; t0 += kBatch * kThreads) {
+            unsigned key[kBatch];
 #pragma unroll
-          for (int j = 0; j < kBatch; ++j) {
-            const int64_t t = t0 + j * kThreads;
-            key[j] = t < T ? cand_key<VALUES>(sh, staged, lo, lh, mask, base, t, t_lo, t_hi) : 0u;
+            for (int j = 0; j < kBatch; ++j) {
+              const int64_t t = t0 + j * kThreads;
+              key[j] = t < T ? cand_key<VALUES>(sh, staged, lo, lh, mask, base, t, t_lo, t_hi) : 0u;
+            }
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j) {
+              const bool on = key[j] != 0u && (key[j] & pmask) == prefix;
+              const unsigned bin = (key[j] >> shift) & 255;
+              if constexpr (decltype(ties)::value) hist_add(hist, on, bin);
+              else if (on) atomicAdd(&hist[bin], 1);
+            }
           }
-#pragma unroll
-          for (int j = 0; j < kBatch; ++j)
-            if (key[j] != 0u && (key[j] & pmask) == prefix) atomicAdd(&hist[(key[j] >> shift) & 255], 1);
-        }
+        };
+        if (cut) sweep(std::true_type{});
+        else sweep(std::false_type{});
         __syncthreads();
       }
       if (wave == 0) {
@@ -260,9 +369,6 @@ __global__ __launch_bounds__(kThreads) void select_kernel(const float* __restric
     // threshold are needed, a first sweep counts them per wave range, so
     // every wave knows how many lie at lower positions.  Winners go to
     // slots in any order: the sort below orders them.
-    const int64_t per_w = ((T + kWaves - 1) / kWaves + 63) / 64 * 64;
-    const int64_t w_beg = wave * per_w;
-    const int64_t w_end = w_beg + per_w < T ? w_beg + per_w : T;
     int eq_before = 0;
     if (!all_ties) {
       int n_eq = 0;
@@ -284,42 +390,30 @@ __global__ __launch_bounds__(kThreads) void select_kernel(const float* __restric
       if (key == thr) take = all_ties || eq_before + lanes_below(eq) < need_ties;
       eq_before += __popcll(eq);
       const unsigned long long tk = __ballot(take);
-      if (tk != 0ull) {
-        int slot0 = 0;
-        if (lane == 0) slot0 = atomicAdd(&sh.n_taken, __popcll(tk));
-        slot0 = __shfl(slot0, 0);
-        if (take) {
-          const int slot = slot0 + lanes_below(tk);
-          if (slot < kThreads)
-            sh.keys[slot] = (static_cast<unsigned long long>(key) << 32) |
-                            static_cast<unsigned long long>(0xFFFFFFFFu - static_cast<unsigned>(t));
-        }
-      }
+      if (tk != 0ull) put(tk, take, key, t);
     }
+    n_keys = kk;
     __syncthreads();
+  }
 
-    // ---- sort, descending, of the kk winners on the key (s, ~t) -----------
+  if (kk > 0) {
+    // ---- sort, descending, of the collected positions on the key (s, ~t) --
     // (padding keys are 0, below every real key: a finite score's key is at
     // least 0x00800000, so every real composite key is positive)
-    if (kk <= 64) {
-      // one wave, one key per lane: a key's place is the number of larger
-      // keys (all composite keys differ in t)
-      if (wave == 0) {
-        const unsigned long long a = lane < kk ? sh.keys[lane] : 0ull;
-        int place = 0;
-        for (int j = 0; j < kk; ++j) {
-          const unsigned hi = static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(a >> 32), j));
-          const unsigned lo32 = static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(a), j));
-          const unsigned long long bj = (static_cast<unsigned long long>(hi) << 32) | lo32;
-          place += bj > a ? 1 : 0;
-        }
-        if (lane < kk) sh.keys[place] = a;
-      }
+    if (n_keys <= 256) {
+      // a key's place is the number of larger keys (all composite keys differ
+      // in t)
+      const unsigned long long a = tid < n_keys ? sh.keys[tid] : 0ull;
+      int place = 0;
+      if (tid < n_keys)
+        for (int j = 0; j < n_keys; ++j) place += sh.keys[j] > a ? 1 : 0;
+      __syncthreads();
+      if (tid < n_keys) sh.keys[place] = a;
       __syncthreads();
     } else {
       int P = 1;
-      while (P < kk) P <<= 1;
-      for (int i = kk + tid; i < P; i += kThreads) sh.keys[i] = 0ull;
+      while (P < n_keys) P <<= 1;
+      for (int i = n_keys + tid; i < P; i += kThreads) sh.keys[i] = 0ull;
       __syncthreads();
       for (int size = 2; size <= P; size <<= 1) {
         for (int stride = size >> 1; stride > 0; stride >>= 1) {
