@@ -64,8 +64,10 @@ size_t hdl_token_logprobs_workspace_size(int64_t n_rows, int64_t d, int64_t voca
  *
  *     logp[n] = z_n[tokens[n]] - log sum_v exp(z_n[v]),   z_n = W_vocab h_n,
  *
- * computed by one fused kernel: the lm-head contraction on bf16 (or fp32)
- * MFMA tiles with fp32 accumulation, an online max / log-sum-exp carried
+ * computed by one fused kernel: the lm-head contraction on bf16 MFMA tiles
+ * with fp32 accumulation (fp32 operands as the six leading products of three
+ * bf16 pieces each: a single product within 3 * 2^-24 of itself, sums as close
+ * to the exact ones as with an fp32 unit), an online max / log-sum-exp carried
  * across vocabulary tiles, and capture of the sampled token's logit.  The
  * n_rows x vocab logits are never written to memory.
  *

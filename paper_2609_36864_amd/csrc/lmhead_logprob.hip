@@ -563,19 +563,29 @@ __device__ __forceinline__ void run_item(const LmheadArgs& p, int64_t row0, int6
   // One K-slice of fp32 operands.  v_mfma_f32_16x16x4_f32 does 157 TFLOP/s on
   // the whole chip, the bf16 form 16 times that, and an fp32 value is the sum
   // of three bf16 values exactly (split3); so each pair of 16-row fragments is
-  // multiplied as the six products of pieces whose orders add up to at most 2
-  // (what is left out is below 2^-26 of |w h|, under the rounding of the fp32
-  // sums), the smallest first.  A slice's 32 K values are one K-step of the
-  // bf16 MFMA: lane group g holds the chunks frag_chunk(g) and
+  // multiplied as the six products of pieces whose orders add up to at most 2,
+  // the smallest first.  The second piece is at most 2^-8 of the value's
+  // leading power and the third 2^-17, so up to 2^-24 of |w h| is left out of a
+  // product (random mantissas: 2^-27 rms), and the bf16 MFMA cuts an
+  // accumulator that is smaller than the products to their last place instead
+  // of rounding it: a logit that is a single product is within 3 x 2^-24 of
+  // itself where the fp32 MFMA is within 2^-24.  In sums, fewer roundings
+  // weigh more: six per 32 products.  Distance to the 64-bit logits in
+  // 2^-24 of them, rms, all products of one sign, d 8, 32, 128, 256, 512, 1024:
+  // fp32 MFMA 0.81, 1.4, 2.7, 3.7, 5.0, 7.2; six products 0.53, 0.52, 1.7,
+  // 2.7, 3.9, 5.0; the same to three places with the products second times
+  // third piece added, for 18 % more time.  A slice's 32 K values are one
+  // K-step of the bf16 MFMA: lane group g holds the chunks frag_chunk(g) and
   // 4 + frag_chunk(g) of W and hidden rows alike.  Pieces are made in
   // registers, where 6 VALU instructions per value run beside the other
   // wave's MFMAs, so HBM and LDS traffic stay those of fp32.  Fragments with
   // a value too large for the split (kSplitMax; an infinite weight would meet
   // the zero pieces of the hidden states) are multiplied by the fp32 MFMA.
   // 2,048 rows, d 1024, V 32,000: 955 -> 682 us (140 -> 197 TFLOP/s of fp32
-  // products, 1.18 PFLOP/s of bf16 ones), distance to the 64-bit result
-  // 6.1e-8 -> 5.7e-8.  Splitting a block between the MFMAs of the one before
-  // it, which 12 more registers allow with a few spills, took 696 us.
+  // products, 1.18 PFLOP/s of bf16 ones), distance of log p and lse to the
+  // 64-bit results 6.1e-8 -> 5.7e-8.  Splitting a block between the MFMAs of
+  // the one before it, which 12 more registers allow with a few spills, took
+  // 696 us.
   [[maybe_unused]] auto slice_f32 = [&](int st, bool next_tail) {
     const int nst = next_stage(st);
     const uint4* abase = &lds[st * R::kStageSlots + wm * 128 * kChunks];
