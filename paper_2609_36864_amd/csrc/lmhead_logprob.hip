@@ -104,6 +104,12 @@ __device__ __forceinline__ Split3 split3(const uint4 (&x)[2]) {
   return s;
 }
 
+// Product o of the six that the split keeps (slice_f32), the smallest first.
+__device__ __forceinline__ void mul_piece(int o, const Split3& a, const Split3& b, f32x4_t& acc) {
+  constexpr int kA[6] = {1, 2, 0, 1, 0, 0}, kB[6] = {1, 0, 2, 0, 1, 0};
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[kA[o]], b.p[kB[o]], acc, 0, 0, 0);
+}
+
 // The largest |x| of the eight values and m (quiet NaNs are passed over).
 // (v_max3_f32 itself: fmaxf would first canonicalise every operand)
 __device__ __forceinline__ float max_abs(const uint4 (&x)[2], float m) {
@@ -113,6 +119,15 @@ __device__ __forceinline__ float max_abs(const uint4 (&x)[2], float m) {
     asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(x[i].z), "v"(x[i].w));
   }
   return m;
+}
+
+// The largest m of the four lanes l, l xor 16, l xor 32, l xor 48 (the lane
+// groups of one row).
+__device__ __forceinline__ float max_groups(float m) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+  m = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
 static_assert(kKSteps == 2, "a K-slice is two K-steps");
@@ -578,9 +593,10 @@ __device__ __forceinline__ void run_item(const LmheadArgs& p, int64_t row0, int6
   // K-step of the bf16 MFMA: lane group g holds the chunks frag_chunk(g) and
   // 4 + frag_chunk(g) of W and hidden rows alike.  Pieces are made in
   // registers, where 6 VALU instructions per value run beside the other
-  // wave's MFMAs, so HBM and LDS traffic stay those of fp32.  Fragments with
+  // wave's MFMAs, so HBM and LDS traffic stay those of fp32.  W fragments with
   // a value too large for the split (kSplitMax; an infinite weight would meet
-  // the zero pieces of the hidden states) are multiplied by the fp32 MFMA.
+  // the zero pieces of the hidden states) are multiplied by the fp32 MFMA, and
+  // so are token rows with one.
   // 2,048 rows, d 1024, V 32,000: 955 -> 682 us (140 -> 197 TFLOP/s of fp32
   // products, 1.18 PFLOP/s of bf16 ones), distance of log p and lse to the
   // 64-bit results 6.1e-8 -> 5.7e-8.  Splitting a block between the MFMAs of
@@ -610,15 +626,43 @@ __device__ __forceinline__ void run_item(const LmheadArgs& p, int64_t row0, int6
         __builtin_amdgcn_sched_barrier(0);
       }
     }
+    // Hidden rows with a value too large for the split.  Which MFMA takes a
+    // row's products must not depend on the other rows of the call, whose bits
+    // it would change: the split sees zeros in the place of such rows, the fp32
+    // MFMA zeros in the place of all others (x + 0 w = x: w is finite there).
+    auto load_rows = [&](int bn, bool large, uint4 (&dst)[2]) {
+      load2(bbase, bn, dst);
+      if ((max_groups(max_abs(dst, 0.f)) >= kSplitMax) != large) dst[0] = dst[1] = make_uint4(0, 0, 0, 0);
+    };
+    const bool large_rows = __any(bmax >= kSplitMax);
+    if (__builtin_expect(large_rows, 0)) {
+#pragma unroll
+      for (int bn = 0; bn < TB; ++bn) {
+        uint4 rb[2];
+        load_rows(bn, false, rb);
+        sb[bn] = split3(rb);
+      }
+    }
 #pragma unroll
     for (int bm = 0; bm < kVB; ++bm) {
       if (__builtin_expect(__any(max_abs(ra, bmax) >= kSplitMax), 0)) {
+        const bool large_w = __any(max_abs(ra, 0.f) >= kSplitMax);
+        if (!large_w) {
+          const Split3 sa = split3(ra);
 #pragma unroll
-        for (int bn = 0; bn < TB; ++bn) {
-          uint4 rb[2];
-          load2(bbase, bn, rb);
-          Mma16<false>::run(ra[0], rb[0], acc[bm][bn]);
-          Mma16<false>::run(ra[1], rb[1], acc[bm][bn]);
+          for (int bn = 0; bn < TB; ++bn)
+#pragma unroll
+            for (int o = 0; o < 6; ++o) mul_piece(o, sa, sb[bn], acc[bm][bn]);
+        }
+        if (large_w || large_rows) {
+#pragma unroll
+          for (int bn = 0; bn < TB; ++bn) {
+            uint4 rb[2];
+            if (large_w) load2(bbase, bn, rb);
+            else load_rows(bn, true, rb);
+            Mma16<false>::run(ra[0], rb[0], acc[bm][bn]);
+            Mma16<false>::run(ra[1], rb[1], acc[bm][bn]);
+          }
         }
         if (bm + 1 < kVB) load2(abase, bm + 1, ra);
       } else {
@@ -627,12 +671,9 @@ __device__ __forceinline__ void run_item(const LmheadArgs& p, int64_t row0, int6
         __builtin_amdgcn_sched_barrier(0);
         // (the TB accumulators in turn: consecutive MFMAs are independent)
 #pragma unroll
-        for (int o = 0; o < 6; ++o) {
-          constexpr int kA[6] = {1, 2, 0, 1, 0, 0}, kB[6] = {1, 0, 2, 0, 1, 0};
+        for (int o = 0; o < 6; ++o)
 #pragma unroll
-          for (int bn = 0; bn < TB; ++bn)
-            acc[bm][bn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sa.p[kA[o]], sb[bn].p[kB[o]], acc[bm][bn], 0, 0, 0);
-        }
+          for (int bn = 0; bn < TB; ++bn) mul_piece(o, sa, sb[bn], acc[bm][bn]);
       }
     }
     wait_vmcnt<(R::kStages - 2) * R::kDma>();

@@ -1,7 +1,7 @@
 """fp32 operands, multiplied as three bf16 pieces each: against the float64
 oracle at fp32's own rounding, and with values that the split cannot take
-(infinities, values that round to infinity in bf16) or whose pieces are zero or
-denormal."""
+(infinities, values that round to infinity in bf16), which leave the other rows'
+bits alone, or whose pieces are zero or denormal."""
 import numpy as np
 import pytest
 import torch
@@ -75,13 +75,44 @@ def test_infinite_hidden_and_positive_infinite_weight(hdl):
     logp, lse = hdl.token_logprobs(H.cuda(), W.cuda(), y.cuda())
     clean, _ = hdl.token_logprobs(H[8:].cuda(), W.cuda(), y[8:].cuda())
     assert torch.isnan(logp[7]) and torch.isnan(lse[7])
-    # (rows that share a fragment with the infinity are multiplied by the fp32
-    # MFMA: both within fp32 rounding of the exact value)
-    mag = (H[8:].abs().double() @ W.abs().double().t()).max(1).values
-    tol = 2 * 2.0 ** -24 * (65 * mag + 64 * 8)
-    assert ((logp[8:].cpu().double() - clean.cpu().double()).abs() <= 2 * tol).all()
+    assert torch.equal(logp[8:], clean)
     H[7, 3] = 1.0
     W[9, 5] = float("inf")
     H[:, 5] = 1.0
     logp, lse = hdl.token_logprobs(H.cuda(), W.cuda(), y.cuda())
     assert torch.isnan(logp).all() and torch.isnan(lse).all()
+
+
+# a row's results have the same bits whatever the other rows hold: rows that
+# the split cannot take, in the first, a middle and the last fragment of a tile
+# (of 64, 128 and 256 rows), with and without weights that it cannot take
+@pytest.mark.parametrize("n", [50, 100, 300])
+@pytest.mark.parametrize("value", [float("inf"), float("nan"), 2.0 ** 60, -3.4e38])
+@pytest.mark.parametrize("weight", [0.01, 2.0 ** 61])
+def test_rows_do_not_depend_on_each_other(hdl, n, value, weight):
+    H, W, y = _inputs(n, 72, 600)
+    W[[3, 130, 599], 30] = weight
+    H[:, 30] = 1e-19
+    ref = hdl.token_logprobs(H.cuda(), W.cuda(), y.cuda(), None, want_entropy=True)
+    bad = [0, 21, n - 1]
+    for r, c in zip(bad, (0, 40, 71)):
+        H[r, c] = value
+    got = hdl.token_logprobs(H.cuda(), W.cuda(), y.cuda(), None, want_entropy=True)
+    keep = torch.ones(n, dtype=torch.bool)
+    keep[bad] = False
+    for a, b in zip(ref, got):
+        assert torch.isfinite(a).all()
+        assert torch.equal(a.cpu()[keep], b.cpu()[keep])
+
+
+# such a row itself: the fp32 MFMA's results for it, one word far above the rest
+@pytest.mark.parametrize("n", [50, 300])
+def test_large_rows(hdl, n):
+    H, W, y = _inputs(n, 72, 600)
+    W[:, 40] = -1e-30 * (1 + torch.arange(600) % 7)
+    H[5, 40] = 1e30   # logits between about -7 and -1 from this column
+    ref_p, ref_l = O.token_logprobs(as_f64(H), as_f64(W), y.numpy())
+    logp, lse = hdl.token_logprobs(H.cuda(), W.cuda(), y.cuda())
+    tol = 2.0 ** -24 * (80 * 30 + 64 * (1 + np.abs(ref_l)))
+    assert (np.abs(lse.cpu().double().numpy() - ref_l) <= tol).all()
+    assert (np.abs(logp.cpu().double().numpy() - ref_p) <= 2 * tol).all()
