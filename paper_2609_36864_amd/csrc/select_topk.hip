@@ -16,12 +16,14 @@
 // them by the composite key (s, ~t) leaves the kk winners first: (s
 // descending, t ascending).
 //
-// Where far more positions reach the bound (equal scores) or kk is large, the
-// kk-th largest s is found by a radix select on the keys instead: four 8-bit
-// digits, most significant first, each resolved from an LDS histogram by one
-// wave.  That yields the threshold score S and how many
-// positions at exactly S are needed.  Each wave then sweeps a contiguous range
-// of positions, its lanes on consecutive positions (coalesced, and spread over
+// Where more maxima than that are equal to the kk-th largest, it is the
+// threshold score S itself unless kk positions lie above it, which one sweep
+// counts (and how many positions at exactly S each wave has).  Where that
+// fails, where too many positions reach the bound (the largest ones all in a
+// few threads) or where kk is large, S is found by a radix select on the keys:
+// four 8-bit digits, most significant first, each resolved from an LDS
+// histogram by one wave.  Each wave then sweeps a contiguous range of
+// positions, its lanes on consecutive positions (coalesced, and spread over
 // the LDS banks), and takes every score above S and, when only some of the
 // positions at S are needed, the lowest-indexed ones (the ties of lower wave
 // ranges are counted first).
@@ -29,7 +31,10 @@
 // Bound by latency: one root is one CU's work.  Scores share a few exponents,
 // so the radix select's histogram adds, which it had to make for every
 // position, mostly met in one LDS word: 4 roots of 32,768 positions, k 32,
-// 36.6 us; collecting above the bound 18.
+// 36.6 us; collecting above the bound 16.5.  k 8, 512 roots of 300 and 256 of
+// 4,096 positions: in no particular order 14.8 -> 11.2 and 11.3 -> 7.6, all
+// equal 16.3 -> 15.4 and 23.0 -> 10.2, all within 0.3 % of each other
+// 15.1 -> 13.5 and 17.0 -> 9.0.
 //
 // Branch-point constraints (the paper applies the same ones to every
 // localization method, Sec. 4.3): candidates may be restricted to a per-root
@@ -48,6 +53,7 @@ namespace {
 
 constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / 64;
+static_assert(kWaves == 16, "a wave for each value of four bits");
 // Roots with at most this many positions keep their candidate keys in LDS
 // after the first pass (128 KB), so the radix passes and the collect pass
 // do not re-read global memory; longer roots recompute them each pass.
@@ -59,9 +65,13 @@ constexpr int kStageMax = 32768;
 constexpr int kCutMax = 128;
 constexpr int kCutMaxLong = 512;
 constexpr int kCutLong = 16384;
+// More maxima than kk + kTieSlack at the bound: it is searched further down
+// than its upper 16 bits, and where that does not help, they are equal.
+constexpr int kTieSlack = 64;
 
 struct Scratch {
   int welig[kWaves];    // candidates per wave
+  int wgt[kWaves];      // positions above the threshold per wave range
   int weq[kWaves];      // positions at the threshold per wave range
   int hist[2][256];     // radix histograms, alternating between digits
   int digit;
@@ -70,7 +80,7 @@ struct Scratch {
   int n_taken;          // winner slots handed out so far
   unsigned long long keys[kThreads];
   unsigned tmax[kThreads];   // each thread's largest candidate key
-  unsigned bound;
+  int reach[8][kWaves];      // per 4-bit step of the bound: maxima that reach it with each value
   int kept;
   unsigned staged[kStageMax];   // candidate key per position, 0 = not a candidate
 };
@@ -88,9 +98,10 @@ __device__ __forceinline__ int lanes_below(unsigned long long m) {
 }
 
 // One more key in `bin` of an LDS histogram for every lane that is on, where
-// many keys are equal: adds to one LDS word go one after the other, so the lanes
-// of the first lane's bin add together (4 roots of 32,768 equal scores 138 ->
-// 59 us; on scores in no particular order it costs 10 %).
+// many keys may be equal: adds to one LDS word go one after the other, so the
+// lanes of the first lane's bin add together (4 roots of 32,768 positions, all
+// equal but 128 larger ones that four threads read, k 64: 91 -> 57 us; on scores
+// in no particular order it costs up to 8 %).
 __device__ __forceinline__ void hist_add(int* hist, bool on, unsigned bin) {
   const unsigned long long m = __ballot(on);
   if (m == 0ull) return;
@@ -249,31 +260,10 @@ __global__ __launch_bounds__(kThreads) void select_kernel(const float* __restric
     }
   };
 
-  int n_keys = 0;   // composite keys in sh.keys, the kk winners among them
-  if (cut && kk > 0) {
-    // ---- the bound: the kk-th largest of the threads' maxima, rounded down
-    // to its upper 16 bits (0 where fewer threads have a candidate) ----------
-    if (wave == 0) {
-      unsigned v[kThreads / 64];
-#pragma unroll
-      for (int i = 0; i < kThreads / 64; ++i) v[i] = sh.tmax[i * 64 + lane];
-      auto reach = [&](unsigned x) {
-        int n = 0;
-#pragma unroll
-        for (int i = 0; i < kThreads / 64; ++i) n += __popcll(__ballot(v[i] >= x));
-        return n;
-      };
-      unsigned bound = 0;
-      for (int bit = 31; bit >= 16; --bit)
-        if (reach(bound | (1u << bit)) >= kk) bound |= 1u << bit;
-      bound = bound > 0u ? bound : 1u;
-      // far more maxima than kk at the bound are ties: nothing to gain
-      const bool ties = reach(bound) > 2 * kk + 128;
-      if (lane == 0) sh.bound = ties ? 0u : bound;
-    }
-    __syncthreads();
-    const unsigned bound = sh.bound;
-    for (int64_t t0 = bound > 0u ? w_beg : w_end; t0 < w_end; t0 += 64 * kBatch) {
+  // Counts the positions above and at thr of every wave range.
+  auto count_at = [&](unsigned thr) {
+    int n_gt = 0, n_eq = 0;
+    for (int64_t t0 = w_beg; t0 < w_end; t0 += 64 * kBatch) {
       unsigned key[kBatch];
 #pragma unroll
       for (int j = 0; j < kBatch; ++j) {
@@ -282,20 +272,82 @@ __global__ __launch_bounds__(kThreads) void select_kernel(const float* __restric
       }
 #pragma unroll
       for (int j = 0; j < kBatch; ++j) {
-        const unsigned long long tk = __ballot(key[j] >= bound);
-        if (tk != 0ull) put(tk, key[j] >= bound, key[j], t0 + j * 64 + lane);
+        n_gt += __popcll(__ballot(key[j] > thr));
+        n_eq += __popcll(__ballot(key[j] == thr));
       }
     }
+    if (lane == 0) {
+      sh.wgt[wave] = n_gt;
+      sh.weq[wave] = n_eq;
+    }
     __syncthreads();
-    n_keys = sh.n_taken;
-    if (n_keys > kThreads) {   // too many: the radix select finds the exact threshold
+  };
+
+  int n_keys = 0;     // composite keys in sh.keys, the kk winners among them
+  unsigned thr = 0;   // the kk-th largest score's key, where it is known
+  int need_ties = 0;  // positions scoring exactly thr to take
+  bool all_ties = false;
+  if (cut && kk > 0) {
+    // ---- the bound: the kk-th largest of the threads' maxima, rounded down
+    // to its upper 16 bits, or further down where many maxima share those
+    // (1 where fewer threads have a candidate).  Four bits at a time: wave w
+    // counts the maxima that reach the bound with w in their place (one wave
+    // trying bit after bit takes 3.5 us for 16 bits, half of a small root) ---
+    unsigned v[kThreads / 64];
+#pragma unroll
+    for (int i = 0; i < kThreads / 64; ++i) v[i] = sh.tmax[i * 64 + lane];
+    unsigned bound = 0;
+    int n = 0;   // maxima that reach the bound
+    for (int shift = 28; shift >= 0 && (shift >= 16 || n > kk + kTieSlack); shift -= 4) {
+      const unsigned x = bound | (static_cast<unsigned>(wave) << shift);
+      int m = 0;
+#pragma unroll
+      for (int i = 0; i < kThreads / 64; ++i) m += __popcll(__ballot(v[i] >= x));
+      if (lane == 0) sh.reach[shift / 4][wave] = m;
       __syncthreads();
-      if (tid == 0) sh.n_taken = 0;
-      n_keys = 0;
+      const int c = sh.reach[shift / 4][lane % kWaves];
+      const unsigned long long in = __ballot(c >= kk) & 0xfffeull;
+      if (in != 0ull) {
+        const int w = 63 - __builtin_clzll(in);
+        bound |= static_cast<unsigned>(w) << shift;
+        n = __builtin_amdgcn_readlane(c, w);
+      }
+    }
+    bound = bound > 0u ? bound : 1u;
+    if (n > kk + kTieSlack) {
+      count_at(bound);
+      int above = 0;
+#pragma unroll
+      for (int i = 0; i < kWaves; ++i) above += sh.wgt[i];
+      if (above < kk) {   // (at least kk positions reach the bound: it is the kk-th largest score)
+        thr = bound;
+        need_ties = kk - above;
+      }
+    } else {
+      for (int64_t t0 = w_beg; t0 < w_end; t0 += 64 * kBatch) {
+        unsigned key[kBatch];
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+          const int64_t t = t0 + j * 64 + lane;
+          key[j] = t < w_end ? cand_key<VALUES>(sh, staged, lo, lh, mask, base, t, t_lo, t_hi) : 0u;
+        }
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+          const unsigned long long tk = __ballot(key[j] >= bound);
+          if (tk != 0ull) put(tk, key[j] >= bound, key[j], t0 + j * 64 + lane);
+        }
+      }
+      __syncthreads();
+      n_keys = sh.n_taken;
+      if (n_keys > kThreads) {   // too many: the radix select finds the exact threshold
+        __syncthreads();
+        if (tid == 0) sh.n_taken = 0;
+        n_keys = 0;
+      }
     }
   }
 
-  if (kk > 0 && n_keys == 0) {
+  if (kk > 0 && n_keys == 0 && thr == 0u) {
     // ---- radix select of the kk-th largest score --------------------------
     // Per digit: one sweep adds the positions that match the prefix so far
     // to this digit's histogram (and clears the other one for the next
@@ -309,7 +361,7 @@ __global__ __launch_bounds__(kThreads) void select_kernel(const float* __restric
       int* hist = sh.hist[dg & 1];
       if (dg > 0 || !staged || cut) {
         if (dg > 0 && tid < 256) sh.hist[(dg + 1) & 1][tid] = 0;
-        auto sweep = [&](auto ties) {   // (ties: the cut gave up on this root)
+        auto sweep = [&](auto ties) {   // (the cut gave up on this root: ties are likely)
           for (int64_t t0 = tid; t0 < T; t0 += kBatch * kThreads) {
             unsigned key[kBatch];
 #pragma unroll
@@ -359,28 +411,22 @@ __global__ __launch_bounds__(kThreads) void select_kernel(const float* __restric
       pmask |= 255u << shift;
       rank = sh.rank;
     }
-    const unsigned thr = prefix;   // bit pattern of the kk-th largest score
-    const int need_ties = rank;    // positions scoring exactly thr to take
-    const bool all_ties = need_ties == sh.n_thr;
+    thr = prefix;   // bit pattern of the kk-th largest score
+    need_ties = rank;
+    all_ties = need_ties == sh.n_thr;
+    if (!all_ties) count_at(thr);
+  }
 
+  if (kk > 0 && n_keys == 0) {
     // ---- collect: all above the threshold, then the lowest-indexed ties ---
     // Wave w owns positions [w per_w, (w + 1) per_w), its lanes taking
     // consecutive positions.  When only some of the positions at the
-    // threshold are needed, a first sweep counts them per wave range, so
+    // threshold are needed, count_at() has counted them per wave range, so
     // every wave knows how many lie at lower positions.  Winners go to
     // slots in any order: the sort below orders them.
     int eq_before = 0;
-    if (!all_ties) {
-      int n_eq = 0;
-      for (int64_t t0 = w_beg; t0 < w_end; t0 += 64) {
-        const int64_t t = t0 + lane;
-        const unsigned key = t < w_end ? cand_key<VALUES>(sh, staged, lo, lh, mask, base, t, t_lo, t_hi) : 0u;
-        n_eq += __popcll(__ballot(key == thr));
-      }
-      if (lane == 0) sh.weq[wave] = n_eq;
-      __syncthreads();
+    if (!all_ties)
       for (int i = 0; i < wave; ++i) eq_before += sh.weq[i];
-    }
     for (int64_t t0 = w_beg; t0 < w_end; t0 += 64) {
       const int64_t t = t0 + lane;
       const unsigned key = t < w_end ? cand_key<VALUES>(sh, staged, lo, lh, mask, base, t, t_lo, t_hi) : 0u;

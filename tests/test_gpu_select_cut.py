@@ -53,3 +53,33 @@ def test_orders_and_ties(hdl, kind, T, k):
         mask[:] = 0
         mask[0, rng.choice(T, k // 2 + 1, replace=False)] = 1
     _check(hdl, np.zeros((1, T), np.float32), d[None], mask, k)
+
+
+# scores within a per cent of each other (next-token entropies near ln V), and
+# many positions at exactly the k-th score: with fewer than k above it, with k
+# and more above it in a few threads' positions only, and at both ends of a wave's
+# range
+@pytest.mark.parametrize("kind", ["narrow", "one narrow", "plateau", "hidden above", "two plateaus"])
+@pytest.mark.parametrize("T,k", [(300, 8), (300, 128), (1024, 100), (1025, 64), (8192, 8), (8192, 128), (20000, 512),
+                                 (32768, 32), (40000, 100)])
+def test_narrow_and_plateaus(hdl, kind, T, k):
+    rng = np.random.default_rng(T + k)
+    v = 11.90 + 0.03 * rng.random((2, T))
+    if kind == "one narrow":
+        v[:, rng.integers(0, T, 3)] = (-4.0, 1e-30, 90.0)
+    elif kind == "plateau":
+        v = np.where(rng.random((2, T)) < 0.5, 2.5, rng.random((2, T)))
+        v[:, rng.choice(T, k // 2, replace=False)] = 3.0 + rng.random((2, k // 2))
+    elif kind == "hidden above":   # (positions 1024 apart belong to one thread)
+        v = np.full((2, T), 2.5)
+        v[:, np.arange(T) % 1024 < 4] = 7.0
+    elif kind == "two plateaus":
+        v = np.where(np.arange(T) % 7 < 3, 2.5, -2.5) * np.ones((2, 1))
+        v[1] = -v[0]
+    v = v.astype(np.float32)
+    mask = (rng.random((2, T)) < 0.9).astype(np.uint8)
+    oi, osc, oc = O.select_by_value(v, mask, k)
+    idx, score, count = hdl.select_top_k(torch.from_numpy(v).cuda(), torch.from_numpy(mask).cuda(), k)
+    assert np.array_equal(count.cpu().numpy(), oc)
+    assert np.array_equal(idx.cpu().numpy(), oi)
+    assert np.array_equal(score.cpu().numpy(), np.asarray(osc, np.float32))
