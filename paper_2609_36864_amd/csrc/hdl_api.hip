@@ -155,13 +155,13 @@ int token_stats(const char* fn, const void* hidden, const void* w_vocab, const i
   for (int64_t r0 = 0; r0 < n_rows; r0 += plan.rows_per_launch) {
     const int64_t n = (n_rows - r0) < plan.rows_per_launch ? (n_rows - r0) : plan.rows_per_launch;
     if (n > plan.n_rows || static_cast<size_t>(plan.n_ch) * static_cast<size_t>(n) > plane ||
-        hdl::plan_launch(plan, n).grid > INT32_MAX)
+        hdl::launch_grid(plan, n) > INT32_MAX)
       return fail(HDL_ERR_UNSUPPORTED, "%s: a launch of %lld rows does not fit the plan", fn,
                   static_cast<long long>(n));
   }
   for (int64_t r0 = 0; r0 < n_rows; r0 += plan.rows_per_launch) {
     const int64_t n = (n_rows - r0) < plan.rows_per_launch ? (n_rows - r0) : plan.rows_per_launch;
-    const hdl::LmheadLaunch lp = hdl::plan_launch(plan, n);
+    const int64_t grid = hdl::launch_grid(plan, n);
     float* logp_c = logp + r0;
     float* lse_c = lse_out ? lse_out + r0 : nullptr;
     float* ent_c = entropy ? entropy + r0 : nullptr;
@@ -189,7 +189,7 @@ int token_stats(const char* fn, const void* hidden, const void* w_vocab, const i
 
     TimedLaunch tl;
     if (timed && (e = tl.start(s)) != hipSuccess) return hip_fail(e, "timing event");
-    e = hdl::launch_lmhead(a, lp.grid, dtype == HDL_BF16, s);
+    e = hdl::launch_lmhead(a, grid, dtype == HDL_BF16, s);
     if (e != hipSuccess) return hip_fail(e, "lm-head kernel launch");
     if ((e = tl.stop(HDL_PROFILE_LMHEAD, s)) != hipSuccess) return hip_fail(e, "timing event");
     e = hdl::launch_merge(a, n, logp_c, lse_c, ent_c, s);
@@ -515,8 +515,8 @@ int hdl_token_logprobs_backward(const void* hidden, const void* w_vocab, const i
     return fail(HDL_ERR_WORKSPACE, "%s: workspace of %zu bytes needed, %zu given", fn, plan.bytes,
                 workspace ? workspace_bytes : static_cast<size_t>(0));
   if (!aligned(workspace, 256)) return fail(HDL_ERR_INVALID_ARG, "%s: workspace must be 256-byte aligned", fn);
-  const hdl::LmheadLaunch grad_launch = hdl::plan_launch(plan.fwd, plan.nc);
-  if (grad_launch.grid > INT32_MAX) return fail(HDL_ERR_UNSUPPORTED, "%s: problem too large for one launch", fn);
+  const int64_t grad_grid = hdl::launch_grid(plan.fwd, plan.nc);
+  if (grad_grid > INT32_MAX) return fail(HDL_ERR_UNSUPPORTED, "%s: problem too large for one launch", fn);
 
   hipStream_t s = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
@@ -564,7 +564,7 @@ int hdl_token_logprobs_backward(const void* hidden, const void* w_vocab, const i
       a.g_cols = plan.v_pad;
       TimedLaunch tg_;
       if ((e = tg_.start(s)) != hipSuccess) return hip_fail(e, "timing event");
-      if ((e = hdl::launch_lmhead_grad(a, grad_launch.grid, s)) != hipSuccess)
+      if ((e = hdl::launch_lmhead_grad(a, grad_grid, s)) != hipSuccess)
         return hip_fail(e, "gradient kernel launch");
       if ((e = tg_.stop(HDL_PROFILE_GRAD, s)) != hipSuccess) return hip_fail(e, "timing event");
       // 2. the chunk's scored hidden rows, gathered chunk-major along the row

@@ -45,13 +45,6 @@ struct ItemGrid {
   int64_t n_rt, n_ch, rows;
 };
 
-// Geometry of one launch over n <= plan.n_rows rows.
-struct LmheadLaunch {
-  int64_t n_rt_max;  // row tiles if every row is scored
-  ItemGrid n_grt;    // its work items if every row is scored
-  int64_t grid;      // workgroups launched: enough for any count of scored rows
-};
-
 __host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 __host__ __device__ inline size_t round_up_sz(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
@@ -147,14 +140,11 @@ __host__ __device__ inline ItemGrid item_grid(int64_t n_s, int64_t n_ch) {
   return ItemGrid{ceil_div(n_s, rows), n_ch, rows};
 }
 
-// Geometry of one launch over n rows (n <= plan.n_rows) with the call's
-// chunking.  The grid has a workgroup for every item of any n_s <= n: whole
-// tiles, at most three half tiles, or, where those are fewer than kNumCu
-// items, narrower ones (at most four times as many).
-inline LmheadLaunch plan_launch(const LmheadPlan& p, int64_t n) {
-  LmheadLaunch l{};
-  l.n_grt = item_grid(n, p.n_ch);
-  l.n_rt_max = l.n_grt.n_rt;
+// Workgroups of one launch over n rows (n <= plan.n_rows) with the call's
+// chunking: one for every item of any n_s <= n, i.e. whole tiles, at most three
+// half tiles, or, where those are fewer than kNumCu items, narrower ones (at
+// most four times as many).
+inline int64_t launch_grid(const LmheadPlan& p, int64_t n) {
   const int64_t halves = ceil_div(n, kTileN / 2);
   int64_t tiles = ceil_div(n, kTileN);
   if (tiles < (halves < 3 ? halves : 3)) tiles = halves < 3 ? halves : 3;
@@ -162,8 +152,7 @@ inline LmheadLaunch plan_launch(const LmheadPlan& p, int64_t n) {
   if (narrow > 4 * kNumCu) narrow = 4 * kNumCu;
   const int64_t items = tiles * p.n_ch > narrow ? tiles * p.n_ch : narrow;
   const int64_t round = kNumXcd * kGroupRT * kGroupCH;
-  l.grid = ceil_div(items, round) * round;
-  return l;
+  return ceil_div(items, round) * round;
 }
 
 // Work item of workgroup b.  The items are put in an order in which any 32

@@ -30,18 +30,19 @@ static long g_cases = 0;
 
 // Every (rt, ch) with rt < n_rt, ch < n_ch is produced by exactly one
 // workgroup of the launch; the others fall outside the problem.
-static void check_coverage(const LmheadPlan& p, const LmheadLaunch& l) {
-  const int64_t n_rt = l.n_rt_max;
+static void check_coverage(const LmheadPlan& p, int64_t n, int64_t grid) {
+  const ItemGrid items = item_grid(n, p.n_ch);   // every row scored
+  const int64_t n_rt = items.n_rt;
   std::vector<int> seen(static_cast<size_t>(n_rt * p.n_ch), 0);
-  for (int64_t b = 0; b < l.grid; ++b) {
+  for (int64_t b = 0; b < grid; ++b) {
     int64_t rt, ch;
-    work_item(b, l.n_grt, &rt, &ch);
+    work_item(b, items, &rt, &ch);
     CHECK(rt >= 0 && ch >= 0, "negative item at b=%lld", (long long)b);
     if (rt < n_rt && ch < p.n_ch) ++seen[static_cast<size_t>(rt * p.n_ch + ch)];
   }
   for (size_t i = 0; i < seen.size(); ++i)
     CHECK(seen[i] == 1, "item %zu covered %d times (n_rt=%lld n_ch=%lld grid=%lld)", i, seen[i],
-          (long long)n_rt, (long long)p.n_ch, (long long)l.grid);
+          (long long)n_rt, (long long)p.n_ch, (long long)grid);
 }
 
 static void check_call(int64_t n_rows, int64_t d, int64_t vocab, int esz, bool coverage) {
@@ -58,16 +59,16 @@ static void check_call(int64_t n_rows, int64_t d, int64_t vocab, int esz, bool c
   CHECK(p.off_rows + sizeof(int32_t) * p.n_rows <= p.off_count, "row list overlaps the counts");
   for (int64_t r0 = 0; r0 < n_rows; r0 += p.rows_per_launch) {
     const int64_t n = n_rows - r0 < p.rows_per_launch ? n_rows - r0 : p.rows_per_launch;
-    const LmheadLaunch l = plan_launch(p, n);
+    const int64_t grid = launch_grid(p, n);
     CHECK(n <= p.n_rows, "launch rows %lld > plan rows %lld", (long long)n, (long long)p.n_rows);
     CHECK(static_cast<size_t>(p.n_ch) * static_cast<size_t>(n) <= plane,
           "n_rows=%lld d=%lld V=%lld esz=%d: launch at %lld needs %lld x %lld partials, plane %zu",
           (long long)n_rows, (long long)d, (long long)vocab, esz, (long long)r0, (long long)p.n_ch,
           (long long)n, plane);
-    CHECK(l.grid <= INT32_MAX && l.grid > 0, "grid %lld", (long long)l.grid);
+    CHECK(grid <= INT32_MAX && grid > 0, "grid %lld", (long long)grid);
     // hidden-state byte offsets of a launch stay below 4 GiB
     CHECK(n * d * esz <= (int64_t{1} << 32), "launch spans %lld bytes", (long long)(n * d * esz));
-    if (coverage) check_coverage(p, l);
+    if (coverage) check_coverage(p, n, grid);
   }
 }
 

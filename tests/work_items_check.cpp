@@ -17,12 +17,12 @@ int main(int argc, char** argv) {
   if (argc != 4) return 2;
   const int64_t n_rows = std::atoll(argv[1]), vocab = std::atoll(argv[2]), d = std::atoll(argv[3]);
   const LmheadPlan p = make_plan(n_rows, vocab, d, 2);
-  const LmheadLaunch l = plan_launch(p, n_rows);
+  const int64_t grid = launch_grid(p, n_rows);
   for (int64_t n_s = 1; n_s <= n_rows; n_s += 1 + n_rows / 199) {
     const ItemGrid g = item_grid(n_s, p.n_ch);
     std::vector<int> seen(static_cast<size_t>(g.n_rt * g.n_ch), 0);
     std::vector<int64_t> share(kNumXcd, 0);
-    for (int64_t b = 0; b < l.grid; ++b) {
+    for (int64_t b = 0; b < grid; ++b) {
       int64_t rt, ch;
       work_item(b, g, &rt, &ch);
       if (rt >= g.n_rt) continue;
