@@ -771,7 +771,7 @@ __global__ __launch_bounds__(kThreads, 1) void lmhead_logprob_kernel(LmheadArgs 
   // ---- work item: XCD-aware (row tile, vocabulary chunk), see plan.h -----
   int64_t n_s = *p.n_scored - p.row_base;
   n_s = n_s < 0 ? 0 : (n_s > p.row_cap ? p.row_cap : n_s);
-  const ItemGrid items = item_grid(n_s, p.n_ch);
+  const ItemGrid items = item_grid(n_s, p.n_ch, BF16);
   int64_t rt, ch;
   work_item(blockIdx.x, items, &rt, &ch);
   if (rt >= items.n_rt) return;

@@ -128,14 +128,22 @@ inline bool make_plan_bounded(int64_t n_rows_total, int64_t vocab, int64_t d, in
 }
 
 // The work items of a launch that scores n_s rows.  Tiles of kTileN rows, but
-//  - of half of that up to 3 / 2 kTileN rows, where a second whole tile would
-//    be mostly padding and W's stream from HBM, not the matrix work, sets the
-//    pace (V = 151,936, d = 2048: 300 rows 271 -> 246 us, 200 rows 224 -> 210;
-//    400 rows would go from 318 to 348);
+//  - of half of that up to 3 / 2 kTileN rows of bf16, where a second whole tile
+//    would be mostly padding and W's stream from HBM, not the matrix work, sets
+//    the pace.  Kernel times, half to whole tiles, statistics: V = 151,936,
+//    130 / 200 / 256 / 300 / 384 rows: d 1024 0.98 / 0.94 / 1.01 / 0.90 / 0.96,
+//    d 2048 0.84 / 0.92 / 0.96 / 0.89 / 0.99, d 5120 0.83 / 0.98 / 1.00 / 0.76 /
+//    0.90 (2048: 300 rows 247 -> 218 us); V = 50,257 and 100,000: 300 rows 0.69
+//    to 0.91, 384 rows 0.83 to 1.08, 256 rows 1.06 to 1.14 at V = 100,000 (two
+//    rounds of workgroups become four); the gradient mode within 0.05 of these.
+//    Rows that are no multiple of 128 bytes (d 1000) range from 0.80 (V =
+//    100,000, 300 rows) to 1.18 (V = 151,936, 340 rows).  fp32 tiles split W's
+//    values on the vector ALU for every row tile anew: 1.03 to 1.06 above 256
+//    rows, 1.3 below (V = 120,000), so they stay whole;
 //  - of half or a quarter where there would be fewer items than CUs (more row
 //    tiles read W more often, but into CUs that would idle).
-__host__ __device__ inline ItemGrid item_grid(int64_t n_s, int64_t n_ch) {
-  int64_t rows = n_s <= kTileN / 2 * 3 ? kTileN / 2 : kTileN;
+__host__ __device__ inline ItemGrid item_grid(int64_t n_s, int64_t n_ch, bool bf16) {
+  int64_t rows = bf16 && n_s <= kTileN / 2 * 3 ? kTileN / 2 : kTileN;
   while (rows > kTileN / 4 && ceil_div(n_s, rows) * n_ch < kNumCu) rows /= 2;
   return ItemGrid{ceil_div(n_s, rows), n_ch, rows};
 }

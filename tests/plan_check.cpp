@@ -30,8 +30,8 @@ static long g_cases = 0;
 
 // Every (rt, ch) with rt < n_rt, ch < n_ch is produced by exactly one
 // workgroup of the launch; the others fall outside the problem.
-static void check_coverage(const LmheadPlan& p, int64_t n, int64_t grid) {
-  const ItemGrid items = item_grid(n, p.n_ch);   // every row scored
+static void check_coverage(const LmheadPlan& p, int64_t n, int64_t grid, bool bf16) {
+  const ItemGrid items = item_grid(n, p.n_ch, bf16);   // every row scored
   const int64_t n_rt = items.n_rt;
   std::vector<int> seen(static_cast<size_t>(n_rt * p.n_ch), 0);
   for (int64_t b = 0; b < grid; ++b) {
@@ -68,7 +68,7 @@ static void check_call(int64_t n_rows, int64_t d, int64_t vocab, int esz, bool c
     CHECK(grid <= INT32_MAX && grid > 0, "grid %lld", (long long)grid);
     // hidden-state byte offsets of a launch stay below 4 GiB
     CHECK(n * d * esz <= (int64_t{1} << 32), "launch spans %lld bytes", (long long)(n * d * esz));
-    if (coverage) check_coverage(p, n, grid);
+    if (coverage) check_coverage(p, n, grid, esz == 2);
   }
 }
 

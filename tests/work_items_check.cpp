@@ -13,13 +13,11 @@
 
 using namespace hdl;
 
-int main(int argc, char** argv) {
-  if (argc != 4) return 2;
-  const int64_t n_rows = std::atoll(argv[1]), vocab = std::atoll(argv[2]), d = std::atoll(argv[3]);
-  const LmheadPlan p = make_plan(n_rows, vocab, d, 2);
+static int check(int64_t n_rows, int64_t vocab, int64_t d, bool bf16) {
+  const LmheadPlan p = make_plan(n_rows, vocab, d, bf16 ? 2 : 4);
   const int64_t grid = launch_grid(p, n_rows);
   for (int64_t n_s = 1; n_s <= n_rows; n_s += 1 + n_rows / 199) {
-    const ItemGrid g = item_grid(n_s, p.n_ch);
+    const ItemGrid g = item_grid(n_s, p.n_ch, bf16);
     std::vector<int> seen(static_cast<size_t>(g.n_rt * g.n_ch), 0);
     std::vector<int64_t> share(kNumXcd, 0);
     for (int64_t b = 0; b < grid; ++b) {
@@ -47,6 +45,13 @@ int main(int argc, char** argv) {
           return std::printf("n_s=%lld run %lld: %zu + %zu tiles\n", (long long)n_s, (long long)run, rts.size(), chs.size()), 1;
       }
   }
+  return 0;
+}
+
+int main(int argc, char** argv) {
+  if (argc != 4) return 2;
+  for (bool bf16 : {true, false})
+    if (check(std::atoll(argv[1]), std::atoll(argv[2]), std::atoll(argv[3]), bf16) != 0) return 1;
   std::printf("ok\n");
   return 0;
 }
