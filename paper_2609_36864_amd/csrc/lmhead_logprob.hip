@@ -610,8 +610,17 @@ __device__ __forceinline__ void run_item(const LmheadArgs& p, int64_t row0, int6
       dst[0] = base[block * 16 * kChunks + frag_lane[0]];
       dst[1] = base[block * 16 * kChunks + frag_lane[1]];
     };
+    // Hidden rows with a value too large for the split.  Which MFMA takes a
+    // row's products must not depend on the other rows of the call, whose bits
+    // it would change: the split sees zeros in the place of such rows, the fp32
+    // MFMA zeros in the place of all others (x + 0 w = x: w is finite there).
+    auto zero_rows = [&](uint4 (&b)[2], bool large) {
+      // (a row is in the four lanes of one r16)
+      if ((max_groups(max_abs(b, 0.f)) >= kSplitMax) == large) b[0] = b[1] = make_uint4(0, 0, 0, 0);
+    };
     Split3 sb[TB];
     float bmax = 0.f;
+    bool large_rows;
     uint4 ra[2];
     {
       uint4 rb[TB][2];
@@ -620,27 +629,16 @@ __device__ __forceinline__ void run_item(const LmheadArgs& p, int64_t row0, int6
       load2(abase, 0, ra);
       next_issue();
 #pragma unroll
-      for (int bn = 0; bn < TB; ++bn) {
-        bmax = max_abs(rb[bn], bmax);
-        sb[bn] = split3(rb[bn]);
-        __builtin_amdgcn_sched_barrier(0);
+      for (int bn = 0; bn < TB; ++bn) bmax = max_abs(rb[bn], bmax);
+      large_rows = __any(bmax >= kSplitMax);
+      if (__builtin_expect(large_rows, 0)) {
+#pragma unroll
+        for (int bn = 0; bn < TB; ++bn) zero_rows(rb[bn], true);
       }
-    }
-    // Hidden rows with a value too large for the split.  Which MFMA takes a
-    // row's products must not depend on the other rows of the call, whose bits
-    // it would change: the split sees zeros in the place of such rows, the fp32
-    // MFMA zeros in the place of all others (x + 0 w = x: w is finite there).
-    auto load_rows = [&](int bn, bool large, uint4 (&dst)[2]) {
-      load2(bbase, bn, dst);
-      if ((max_groups(max_abs(dst, 0.f)) >= kSplitMax) != large) dst[0] = dst[1] = make_uint4(0, 0, 0, 0);
-    };
-    const bool large_rows = __any(bmax >= kSplitMax);
-    if (__builtin_expect(large_rows, 0)) {
 #pragma unroll
       for (int bn = 0; bn < TB; ++bn) {
-        uint4 rb[2];
-        load_rows(bn, false, rb);
-        sb[bn] = split3(rb);
+        sb[bn] = split3(rb[bn]);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
 #pragma unroll
@@ -658,8 +656,8 @@ __device__ __forceinline__ void run_item(const LmheadArgs& p, int64_t row0, int6
 #pragma unroll
           for (int bn = 0; bn < TB; ++bn) {
             uint4 rb[2];
-            if (large_w) load2(bbase, bn, rb);
-            else load_rows(bn, true, rb);
+            load2(bbase, bn, rb);
+            if (!large_w) zero_rows(rb, false);
             Mma16<false>::run(ra[0], rb[0], acc[bm][bn]);
             Mma16<false>::run(ra[1], rb[1], acc[bm][bn]);
           }
