@@ -889,9 +889,16 @@ hipError_t launch_merge(const LmheadArgs& a, int64_t n_rows, float* logp, float*
   const int64_t blocks = (n_rows + kMergeRows - 1) / kMergeRows;
   if (blocks <= 0) return hipSuccess;
   const dim3 g(static_cast<unsigned>(blocks));
-  // 32 segments where each still has at least two chunks, else 8 (256-thread
-  // workgroups, whose fewer LDS states cost many rows less)
-  const bool wide = a.n_ch >= 64;
+  // 8 or 32 segments per row.  32 shorten the chain of loads at the cost of more
+  // LDS states and more steps for the row's first thread, more so with the
+  // entropy's larger states; the line is the same with it, since it decides the
+  // order of the sums and log p must not depend on the entropy.  Whole calls at
+  // d 64, 8 -> 32 segments, us: 512 rows 14.9 -> 15.8 at 32 chunks, 17.9 -> 18.4
+  // at 64, 24.4 -> 23.9 at 96, 26.2 -> 25.0 at 120, 65 -> 55 at 594; 8,192 rows
+  // 77.0 -> 77.7 at 64, 111.4 -> 111.6 at 96, 469 -> 466 at 594; with the entropy
+  // 512 rows 19.1 -> 22.3 at 64, 27.7 -> 29.8 at 120, 37.7 -> 37.1 at 256, 73 ->
+  // 67 at 594.
+  const bool wide = a.n_ch >= 96;
   if (entropy) {
     if (wide) hipLaunchKernelGGL((merge_kernel<32, true>), g, dim3(kMergeRows * 32), 0, stream, a, logp, lse, entropy);
     else hipLaunchKernelGGL((merge_kernel<8, true>), g, dim3(kMergeRows * 8), 0, stream, a, logp, lse, entropy);
