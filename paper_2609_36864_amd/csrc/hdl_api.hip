@@ -413,7 +413,7 @@ BwdPlan make_bwd_plan(int64_t n_rows, int64_t vocab, int64_t d) {
   const int64_t tiles = (p.nc / hdl::kTileN) * ((d + hdl::kTileN - 1) / hdl::kTileN);
   const int64_t slices = p.v_pad / 64;
   int64_t s = 1, best = 0;
-  for (int64_t c = 1; c == 1 || (c <= 64 && 2 * c <= slices); ++c) {   // (2 slices each at least)
+  for (int64_t c = 1; c == 1 || (c <= 64 && 2 * c <= slices); ++c) {   // (2 slices each on average)
     const int64_t cost = hdl::ceil_div(tiles * c, hdl::kNumCu) * (hdl::ceil_div(slices, c) + 40);
     if (c == 1 || cost < best) {
       s = c;

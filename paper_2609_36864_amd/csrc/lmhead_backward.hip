@@ -221,7 +221,10 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_kernel(GemmArgs p) {
 
   // ---- work item: XCD-aware (m-tile, n-tile, split) ----------------------
   // Workgroups go to the XCDs round-robin; run r of 32 items is the next 32
-  // workgroups of XCD r mod 8, so every XCD gets an equal share (gemm_item).
+  // workgroups of XCD r mod 8, so every XCD gets an equal share of the launch's
+  // items (gemm_item).  The scored rows are known on the device only: dH tiles
+  // past them end at once, wherever they lie (4,096 rows, d 4096, 46 % of them
+  // scored: four XCDs hold 32 live items each, the others none).
   int64_t tm, tn, split;
   const int64_t j = blockIdx.x / kNumXcd;
   if (!gemm_item(((j / 32) * kNumXcd + blockIdx.x % kNumXcd) * 32 + j % 32, p, &tm, &tn, &split)) return;

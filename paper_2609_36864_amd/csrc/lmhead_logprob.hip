@@ -520,8 +520,8 @@ __device__ __forceinline__ void run_item(const LmheadArgs& p, int64_t row0, int6
   // K-step 0, one hidden-state fragment of K-step 1 (fb[1]).  The slice's
   // last quarter waits for the next slice's DMA and the workgroup barrier,
   // reads the next slice's first W fragments and all of its K-step-0 hidden
-  // fragments (fb[0]), and issues the DMA of the slice after next into the
-  // stage just released, spread between its MFMAs.
+  // fragments (fb[0]), and issues the DMAs of the slice kStages on into the
+  // stage just released, beside its first MFMAs.
   const int n_pre = n_iter < R::kStages ? n_iter : R::kStages;
   for (int sl = 0; sl < n_pre; ++sl) {
     next_issue();
@@ -762,6 +762,11 @@ __device__ __forceinline__ void run_item(const LmheadArgs& p, int64_t row0, int6
   }
 }
 
+// Two workgroup waves per SIMD have 256 VGPRs each.  Statistics and entropy take
+// 232 to 240 of them in bf16; the fp32 instantiations, whose split hidden rows
+// take 48, spill 13 to 21 and the gradient ones 2, all stored before the V-tile
+// loop and read back outside the K loop, once per V-tile (after its last slice,
+// where a reload also waits for the DMAs in flight) or after the last one.
 template <bool BF16, bool KTAIL, int EPI>
 __global__ __launch_bounds__(kThreads, 1) void lmhead_logprob_kernel(LmheadArgs p) {
   __shared__ uint4 lds[kLdsSlots];   // a ring of [W | hidden] stages, see Ring
