@@ -384,7 +384,7 @@ namespace {
 // (bf16), exists for one chunk at a time, never more.
 struct BwdPlan {
   int64_t nc, v_pad, n_chunks;
-  int64_t splits, k_split;      // vocabulary split of the dH contraction
+  int64_t splits;               // vocabulary split of the dH contraction, every row scored
   hdl::LmheadPlan fwd;          // gradient-mode lm-head launches (nc rows)
   size_t off_rows, off_count, off_g, off_hc, off_hpart, bytes;
 };
@@ -403,25 +403,14 @@ BwdPlan make_bwd_plan(int64_t n_rows, int64_t vocab, int64_t d) {
   p.n_chunks = (n_rows + p.nc - 1) / p.nc;
   // dH = G W has nc/256 x d/256 output tiles, each a sum over the whole
   // vocabulary; it is split so that the CUs, one workgroup each, run out of
-  // work together.  A round of workgroups costs its K-slices and, per split,
-  // about 40 slices' time of pipeline fill and of partial sums written and read
-  // back.  Whole calls at the chosen split against 8 (the most there were):
+  // work together (best_split; a mask that leaves fewer rows gets more splits in
+  // the same memory, dh_live).  Whole calls at the chosen split against 8 (the most there were):
   // 300 rows, d 2048, V 151,936: 16 splits 928 us, 8 (128 workgroups) 1122;
   // 700 rows: 10 splits (240) 1448, 11 (264) 1686, 8 1509; 3,000 rows, d 1024,
   // V 32,000: 5 (240) 556, 6 (288) 657, 8 (384) 611; 5,000 rows, d 2048,
   // V 151,936: 3 (480) 7697, 4 (640) 8117.
-  const int64_t tiles = (p.nc / hdl::kTileN) * ((d + hdl::kTileN - 1) / hdl::kTileN);
-  const int64_t slices = p.v_pad / 64;
-  int64_t s = 1, best = 0;
-  for (int64_t c = 1; c == 1 || (c <= 64 && 2 * c <= slices); ++c) {   // (2 slices each on average)
-    const int64_t cost = hdl::ceil_div(tiles * c, hdl::kNumCu) * (hdl::ceil_div(slices, c) + 40);
-    if (c == 1 || cost < best) {
-      s = c;
-      best = cost;
-    }
-  }
-  p.k_split = (slices + s - 1) / s * 64;
-  p.splits = (p.v_pad + p.k_split - 1) / p.k_split;
+  const int64_t tiles_m = p.nc / hdl::kTileV;
+  p.splits = hdl::best_split(tiles_m, (d + hdl::kTileN - 1) / hdl::kTileN, p.v_pad / 64, INT64_MAX);
   p.fwd = hdl::make_plan(p.nc, vocab, d, 2);
   size_t off = 0;
   p.off_rows = off;
@@ -522,6 +511,7 @@ int hdl_token_logprobs_backward(const void* hidden, const void* w_vocab, const i
   char* ws = static_cast<char*>(workspace);
   int32_t* rows = reinterpret_cast<int32_t*>(ws + plan.off_rows);
   int32_t* n_scored = reinterpret_cast<int32_t*>(ws + plan.off_count);
+  int32_t* live = n_scored + 1;   // (64 integers lie before the count pass's)
   uint16_t* g = reinterpret_cast<uint16_t*>(ws + plan.off_g);
   uint16_t* hc = reinterpret_cast<uint16_t*>(ws + plan.off_hc);
   float* hpart = reinterpret_cast<float*>(ws + plan.off_hpart);
@@ -570,7 +560,8 @@ int hdl_token_logprobs_backward(const void* hidden, const void* w_vocab, const i
       // 2. the chunk's scored hidden rows, gathered chunk-major along the row
       // index (zeros up to the next 64 rows)
       if ((e = hdl::launch_gather_rows_cm(static_cast<const uint16_t*>(hidden_b), d, rows + base, n_scored, base,
-                                          plan.nc, d, hc, s)) != hipSuccess)
+                                          plan.nc, d, hc, plan.v_pad / 64, plan.splits * (plan.nc / hdl::kTileV),
+                                          live, s)) != hipSuccess)
         return hip_fail(e, "row gather launch");
       // 3. dH rows of the chunk: G W (W read as stored, K = vocabulary rows past
       // V clamped: G is zero there), split along the vocabulary, partials summed in order
@@ -579,15 +570,13 @@ int hdl_token_logprobs_backward(const void* hidden, const void* w_vocab, const i
       gh.dyn = n_scored;
       gh.dyn_base = base;
       gh.dyn_dim = 1;
-      gh.k_split = plan.k_split;
+      gh.live = live;
       gh.splits = plan.splits;
-      gh.c_split_stride = plan.nc * d;
       TimedLaunch th_;
       if ((e = th_.start(s)) != hipSuccess) return hip_fail(e, "timing event");
       if ((e = hdl::launch_gemm(gh, s)) != hipSuccess) return hip_fail(e, "GEMM launch");
       if ((e = th_.stop(HDL_PROFILE_GEMM, s)) != hipSuccess) return hip_fail(e, "timing event");
-      if ((e = hdl::launch_splitk_scatter(hpart, plan.splits, plan.nc * d, d, rows + base, n_scored, base,
-                                          plan.nc, dh_b, s)) != hipSuccess)
+      if ((e = hdl::launch_splitk_scatter(hpart, live, d, rows + base, n_scored, base, plan.nc, dh_b, s)) != hipSuccess)
         return hip_fail(e, "split-K sum launch");
       // 4. dW (+)= G^T H over the chunk's rows (both read with the row index as
       // K); the call's first chunk overwrites dW unless the caller accumulates

@@ -63,17 +63,55 @@ struct GemmArgs {
   int b_layout;
   int64_t b_cols, b_krows;
   int64_t m, n, k;          // sizes (upper bounds when a dimension is dynamic)
-  // Dynamic dimension: dyn_dim 1 makes M = clamp(*dyn - dyn_base, 0, m);
+  // Dynamic dimension: dyn_dim 1 makes M = clamp(*dyn - dyn_base, 0, m), with
+  // as many splits of K as live[0] says (dh_split);
   // dyn_dim 2 makes K = round_up(clamp(*dyn - dyn_base, 0, k), 64).
   const int32_t* dyn;
   int64_t dyn_base;
   int dyn_dim;
+  const int32_t* live;
   int64_t k_split;          // K elements per split (multiple of 64)
   int64_t tiles_m, tiles_n, splits, gm, gn;   // launch grouping (host-computed)
   float* c;
   int64_t ldc, c_split_stride;
   int beta;                 // 0: store, 1: accumulate
 };
+
+// The splits of dH's contraction (vocabulary slices of 64) into c sums for
+// `tiles` output tiles, one workgroup per tile and split: what the c-way split
+// costs, in slices.  A round of workgroups costs its K-slices and, per split,
+// about 40 slices' time of pipeline fill and of partial sums written and read
+// back.
+constexpr int kMaxSplits = 64;
+__host__ __device__ inline bool split_fits(int64_t c, int64_t slices) {   // (2 slices each on average)
+  return c == 1 || (c <= kMaxSplits && 2 * c <= slices);
+}
+__host__ __device__ inline int64_t split_cost(int64_t tiles, int64_t slices, int64_t c) {
+  return ceil_div(tiles * c, kNumCu) * (ceil_div(slices, c) + 40);
+}
+// The cheapest split of a contraction whose partial sums may fill at most
+// `room` tile rows: tiles_m c <= room.
+__host__ __device__ inline int64_t best_split(int64_t tiles_m, int64_t tiles_n, int64_t slices, int64_t room) {
+  int64_t s = 1, best = split_cost(tiles_m * tiles_n, slices, 1);
+  for (int64_t c = 2; split_fits(c, slices) && tiles_m * c <= room; ++c) {
+    const int64_t cost = split_cost(tiles_m * tiles_n, slices, c);
+    if (cost < best) {
+      s = c;
+      best = cost;
+    }
+  }
+  return s;
+}
+// dH's launch for the scored rows there are, n of at most p.m: their tiles and
+// the split made for them, in the memory and the grid of the split made for
+// p.m rows (splits tiles_m tile rows).
+__host__ __device__ inline void dh_live(GemmArgs* p, int64_t n, int64_t splits) {
+  p->tiles_m = ceil_div(n, kTileV);
+  p->gm = p->gm < p->tiles_m ? p->gm : p->tiles_m;
+  p->splits = splits;
+  p->k_split = ceil_div(p->k / 64, splits) * 64;
+  p->c_split_stride = p->tiles_m * kTileV * p->ldc;
+}
 
 // Item `at` of the launch: gm x gn tiles of one split after the other, which
 // share A and B rows through an XCD's L2 (smaller groups at the edges, no
@@ -109,12 +147,15 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t stream);
 // n = clamp(*dyn - dyn_base, 0, cap), stored chunk-major along e:
 // X[e][j] at ((e / 8) * d + j) * 8 + e % 8 (kLayoutCmRow with ld = d).
 // out holds cap * d bf16; d % 8 == 0, cap % 8 == 0.
+// Also leaves in live[0] the split of dH for n rows (slices: vocabulary slices
+// of 64, room: tile rows that the partial sums have).
 hipError_t launch_gather_rows_cm(const uint16_t* in, int64_t ld_in, const int32_t* map, const int32_t* dyn,
-                                 int64_t dyn_base, int64_t cap, int64_t d, uint16_t* out, hipStream_t stream);
-// dh[map[e]][j] = sum_s part[s][e][j] for e < clamp(*dyn - dyn_base, 0, cap)
-hipError_t launch_splitk_scatter(const float* part, int64_t splits, int64_t split_stride, int64_t d,
-                                 const int32_t* map, const int32_t* dyn, int64_t dyn_base, int64_t cap,
-                                 float* dh, hipStream_t stream);
+                                 int64_t dyn_base, int64_t cap, int64_t d, uint16_t* out, int64_t slices, int64_t room,
+                                 int32_t* live, hipStream_t stream);
+// dh[map[e]][j] = sum_{s < live[0]} part[s][e][j] for e < n = clamp(*dyn -
+// dyn_base, 0, cap), the parts n rows, rounded up to tiles, apart
+hipError_t launch_splitk_scatter(const float* part, const int32_t* live, int64_t d, const int32_t* map,
+                                 const int32_t* dyn, int64_t dyn_base, int64_t cap, float* dh, hipStream_t stream);
 // dh[n][:] = 0 for rows with mask[n] == 0
 hipError_t launch_zero_masked_rows(const uint8_t* mask, int64_t n_rows, int64_t d, float* dh,
                                    hipStream_t stream);

@@ -221,10 +221,20 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_kernel(GemmArgs p) {
 
   // ---- work item: XCD-aware (m-tile, n-tile, split) ----------------------
   // Workgroups go to the XCDs round-robin; run r of 32 items is the next 32
-  // workgroups of XCD r mod 8, so every XCD gets an equal share of the launch's
-  // items (gemm_item).  The scored rows are known on the device only: dH tiles
-  // past them end at once, wherever they lie (4,096 rows, d 4096, 46 % of them
-  // scored: four XCDs hold 32 live items each, the others none).
+  // workgroups of XCD r mod 8, so every XCD gets an equal share (gemm_item).
+  int64_t m_valid = p.m, k_valid = p.k;
+  if (p.dyn_dim != 0) {
+    int64_t dv = *p.dyn - p.dyn_base;
+    const int64_t cap = p.dyn_dim == 1 ? p.m : p.k;
+    dv = dv < 0 ? 0 : (dv > cap ? cap : dv);
+    if (p.dyn_dim == 1) {
+      if (dv == 0) return;
+      m_valid = dv;
+      dh_live(&p, dv, p.live[0]);
+    } else {
+      k_valid = (dv + kGemmSliceK - 1) / kGemmSliceK * kGemmSliceK;
+    }
+  }
   int64_t tm, tn, split;
   const int64_t j = blockIdx.x / kNumXcd;
   if (!gemm_item(((j / 32) * kNumXcd + blockIdx.x % kNumXcd) * 32 + j % 32, p, &tm, &tn, &split)) return;
@@ -234,15 +244,6 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_kernel(GemmArgs p) {
   tm = __builtin_amdgcn_readfirstlane(static_cast<int>(tm));
   tn = __builtin_amdgcn_readfirstlane(static_cast<int>(tn));
 
-  int64_t m_valid = p.m, k_valid = p.k;
-  if (p.dyn_dim != 0) {
-    int64_t dv = *p.dyn - p.dyn_base;
-    const int64_t cap = p.dyn_dim == 1 ? p.m : p.k;
-    dv = dv < 0 ? 0 : (dv > cap ? cap : dv);
-    if (p.dyn_dim == 1) m_valid = dv;
-    else k_valid = (dv + kGemmSliceK - 1) / kGemmSliceK * kGemmSliceK;
-  }
-  if (tm * kTileV >= m_valid) return;
   const int64_t k0 = split * p.k_split;
   const int64_t k1 = (k0 + p.k_split < k_valid) ? k0 + p.k_split : k_valid;
   const int n_iter = k1 > k0 ? static_cast<int>((k1 - k0) / kGemmSliceK) : 0;
@@ -380,13 +381,32 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_kernel(GemmArgs p) {
 // out[(e / 8) * d + j][e % 8] = in[map[e]][j] for the e < n scored rows,
 // zeros for n <= e < round_up(n, 64).  Each thread moves an 8 x 8 block
 // (8 rows x 8 columns): eight 16-byte row reads, eight 16-byte writes of one
-// column's 8 rows each.
+// column's 8 rows each.  The first wave also leaves the split of dH for n rows
+// (best_split, each lane the cost of one number of splits) in live[0]: chosen
+// for the rows of the call instead, a mask left most of the chip idle (both GEMMs
+// together at V 151,936, 10 % / 46 % of the rows scored, us: 4,096 rows, d 4096
+// 4147 -> 1445 / 6027 -> 4196; 8,192 rows, d 2048 3912 -> 1171 / 5752 -> 3861;
+// V 32,000, 3,000 rows, d 1024 196 -> 92 / 259 -> 195).
 __global__ __launch_bounds__(256) void gather_rows_cm_kernel(const uint16_t* __restrict__ in, int64_t ld_in,
                                                              const int32_t* __restrict__ map,
                                                              const int32_t* __restrict__ dyn, int64_t dyn_base,
-                                                             int64_t cap, int64_t d, uint16_t* __restrict__ out) {
+                                                             int64_t cap, int64_t d, uint16_t* __restrict__ out,
+                                                             int64_t slices, int64_t room, int32_t* __restrict__ live) {
   int64_t n = *dyn - dyn_base;
   n = n < 0 ? 0 : (n > cap ? cap : n);
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kMaxSplits) {
+    static_assert(kMaxSplits == 64, "a lane for each number of splits");
+    const int64_t c = threadIdx.x + 1, tiles_m = ceil_div(n, kTileV);
+    int64_t key = INT64_MAX;   // cost, then the number of splits
+    if (c == 1 || (split_fits(c, slices) && tiles_m * c <= room))
+      key = split_cost(tiles_m * ceil_div(d, kTileN), slices, c) * kMaxSplits + (c - 1);
+#pragma unroll
+    for (int x = 1; x < 64; x <<= 1) {
+      const int64_t o = __shfl_xor(static_cast<long long>(key), x);
+      key = key < o ? key : o;
+    }
+    if (threadIdx.x == 0) live[0] = static_cast<int32_t>(key % kMaxSplits) + 1;
+  }
   int64_t n_pad = (n + 63) / 64 * 64;
   n_pad = n_pad < cap ? n_pad : cap;
   const int64_t e0 = static_cast<int64_t>(blockIdx.y) * 8;
@@ -412,8 +432,8 @@ __global__ __launch_bounds__(256) void gather_rows_cm_kernel(const uint16_t* __r
 }
 
 // dh[map[e]][j] = sum over splits s (in order) of part[s][e][j].
-__global__ __launch_bounds__(256) void splitk_scatter_kernel(const float* __restrict__ part, int64_t splits,
-                                                             int64_t split_stride, int64_t d,
+__global__ __launch_bounds__(256) void splitk_scatter_kernel(const float* __restrict__ part,
+                                                             const int32_t* __restrict__ live, int64_t d,
                                                              const int32_t* __restrict__ map,
                                                              const int32_t* __restrict__ dyn, int64_t dyn_base,
                                                              int64_t cap, float* __restrict__ dh) {
@@ -423,9 +443,11 @@ __global__ __launch_bounds__(256) void splitk_scatter_kernel(const float* __rest
   if (e >= n_valid) return;
   const int64_t j = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) * 4;
   if (j >= d) return;
+  const int splits = live[0];
+  const int64_t split_stride = ceil_div(n_valid, kTileV) * kTileV * d;
   const float* src = part + e * d + j;
   float4 acc = *reinterpret_cast<const float4*>(src);
-  for (int64_t s = 1; s < splits; ++s) {
+  for (int s = 1; s < splits; ++s) {
     const float4 v = *reinterpret_cast<const float4*>(src + s * split_stride);
     acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
   }
@@ -457,22 +479,22 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t stream) {
 }
 
 hipError_t launch_gather_rows_cm(const uint16_t* in, int64_t ld_in, const int32_t* map, const int32_t* dyn,
-                                 int64_t dyn_base, int64_t cap, int64_t d, uint16_t* out, hipStream_t stream) {
+                                 int64_t dyn_base, int64_t cap, int64_t d, uint16_t* out, int64_t slices, int64_t room,
+                                 int32_t* live, hipStream_t stream) {
   const int64_t gx = (d / 8 + 255) / 256;
   const int64_t gy = (cap + 7) / 8;
   if (gx <= 0 || gy <= 0) return hipSuccess;
   hipLaunchKernelGGL(gather_rows_cm_kernel, dim3(static_cast<unsigned>(gx), static_cast<unsigned>(gy)), dim3(256), 0,
-                     stream, in, ld_in, map, dyn, dyn_base, cap, d, out);
+                     stream, in, ld_in, map, dyn, dyn_base, cap, d, out, slices, room, live);
   return hipGetLastError();
 }
 
-hipError_t launch_splitk_scatter(const float* part, int64_t splits, int64_t split_stride, int64_t d,
-                                 const int32_t* map, const int32_t* dyn, int64_t dyn_base, int64_t cap,
-                                 float* dh, hipStream_t stream) {
+hipError_t launch_splitk_scatter(const float* part, const int32_t* live, int64_t d, const int32_t* map,
+                                 const int32_t* dyn, int64_t dyn_base, int64_t cap, float* dh, hipStream_t stream) {
   const int64_t gx = (d / 4 + 255) / 256;
   if (gx <= 0 || cap <= 0) return hipSuccess;
   hipLaunchKernelGGL(splitk_scatter_kernel, dim3(static_cast<unsigned>(gx), static_cast<unsigned>(cap)), dim3(256),
-                     0, stream, part, splits, split_stride, d, map, dyn, dyn_base, cap, dh);
+                     0, stream, part, live, d, map, dyn, dyn_base, cap, dh);
   return hipGetLastError();
 }
 

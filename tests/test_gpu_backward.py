@@ -174,3 +174,26 @@ def test_backward_full_size_every_row_tile(hdl):
     bound = 2.0 ** -7 * (np.abs(up.double().numpy()[keep])[:, None] * np.abs(as_f64(H)[keep])).sum(0)
     colsum = dw.sum(axis=0)
     assert np.all(np.abs(colsum) <= bound + 1e-6 * np.abs(dw).max())
+
+
+# scored rows that fill 0, 1, 2 and 3 of the call's tiles of 256 rows, at their
+# edges: dH takes more splits of the vocabulary the fewer there are, in the same
+# workspace (nothing behind it is touched)
+@pytest.mark.parametrize("scored", [0, 1, 255, 256, 257, 512, 513, 700])
+@pytest.mark.parametrize("d,V", [(136, 9000), (520, 1500)])
+def test_splits_for_scored_rows(hdl, scored, d, V):
+    n = 700
+    H, W, y, m, up = _case(n, d, V, seed=scored + d)
+    m.zero_()
+    m[torch.randperm(n, generator=torch.Generator().manual_seed(scored))[:scored]] = 1
+    need = hdl.backward_workspace_size(n, d, V)
+    ws = torch.full((need + 4096,), 0xAB, dtype=torch.uint8, device="cuda")
+    dh, dw = _gpu(hdl, H, W, y, m, up, workspace=ws[:need])
+    assert (ws[need:] == 0xAB).all()
+    want_h, want_w, mag_h, mag_w = O.token_logprobs_backward(as_f64(H), as_f64(W), y.numpy(), up.double().numpy(),
+                                                             mask=m.numpy())
+    if scored == 0:
+        assert not dh.any() and not dw.any()
+    else:
+        _check(dh, want_h, mag_h, "dH")
+        _check(dw, want_w, mag_w, "dW")
