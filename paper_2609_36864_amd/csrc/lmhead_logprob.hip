@@ -839,7 +839,9 @@ __global__ __launch_bounds__(kMergeRows * SEG) void merge_kernel(LmheadArgs p, f
   if (seg != 0 || e >= n_s) return;
   const int n_seg = p.n_ch < SEG ? static_cast<int>(p.n_ch) : SEG;
   for (int i = 1; i < n_seg; ++i) combine(m, s, z, t, xm[i][r], xs[i][r], xz[i][r], ENT ? xt[i][r] : 0.f);
-  const float lse = m + __builtin_amdgcn_logf(s) * 0.6931471805599453f;
+  // (no logit above -inf, as an infinite hidden state can leave them in one
+  // vocabulary tile: NaN like where some are +inf)
+  const float lse = m == kNegInf ? __builtin_nanf("") : m + __builtin_amdgcn_logf(s) * 0.6931471805599453f;
   const int row = p.rows[e];
   const int y = p.tokens[row];
   float lp = z - lse;

@@ -533,3 +533,20 @@ def test_remainder_launch_keeps_the_call_chunking(hdl):
     assert err.max() <= TOL_BF16
     assert np.abs(lse[idx].cpu().numpy() - want_lse).max() <= TOL_BF16
     assert np.abs(ent[idx].cpu().numpy() - O.token_entropy(Hs, Wd)).max() <= TOL_BF16
+
+
+# an infinite hidden element that meets weights of one sign: every logit of its
+# row is -inf (or +inf), in one vocabulary tile, several, and a ragged last one
+@pytest.mark.parametrize("sign", [-1.0, 1.0])
+@pytest.mark.parametrize("V", [100, 256, 700])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_infinite_logits_of_one_sign(hdl, V, sign, dtype):
+    g = torch.Generator().manual_seed(V)
+    H = torch.randn(70, 64, generator=g)
+    W = torch.randn(V, 64, generator=g) * 0.05
+    W[:, 5] = 0.01 + W[:, 5].abs()
+    H[[0, 66], 5] = sign * float("inf")
+    y = torch.randint(0, V, (70,), generator=g, dtype=torch.int32)
+    logp, lse, ent = hdl.token_logprobs(H.to(dtype).cuda(), W.to(dtype).cuda(), y.cuda(), None, want_entropy=True)
+    for x in (logp, lse):
+        assert torch.isnan(x[[0, 66]]).all() and torch.isfinite(x[1:66]).all() and torch.isfinite(x[67:]).all()
