@@ -60,3 +60,16 @@ def test_row_tile_edges_backward(hdl, n):
     assert (np.abs(dh.cpu().numpy() - ref_h) <= grad_tol(mag_h)).all()
     assert (np.abs(dw.cpu().numpy() - ref_w) <= grad_tol(mag_w)).all()
 
+
+# the merge's two numbers of chunk segments at their line (96 chunks of one
+# vocabulary tile each): against the oracle, log p and lse with the same bits
+# whether the entropy is computed or not
+@pytest.mark.parametrize("chunks", [9, 95, 96, 97])
+@pytest.mark.parametrize("n", [40, 300])
+def test_merge_segments(hdl, chunks, n):
+    H, W, y = _inputs(n, 64, 256 * chunks - 3, torch.bfloat16, seed=chunks)
+    ref_p, ref_l = O.token_logprobs(as_f64(H), as_f64(W), y.numpy())
+    plain = hdl.token_logprobs(H.cuda(), W.cuda(), y.cuda())
+    logp, lse, _ = hdl.token_logprobs(H.cuda(), W.cuda(), y.cuda(), None, want_entropy=True)
+    assert torch.equal(plain[0], logp) and torch.equal(plain[1], lse)
+    assert np.abs(logp.cpu().numpy() - ref_p).max() <= 2e-3 and np.abs(lse.cpu().numpy() - ref_l).max() <= 2e-3
