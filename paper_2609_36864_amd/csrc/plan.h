@@ -60,16 +60,19 @@ inline int64_t rows_per_launch(int64_t d, int esz) {
 // the tail across 256 CUs.  Aim for about 32 items per CU (measured: at
 // 16,384 rows this runs 6 % faster than 8 items per CU; at 65,536 rows both
 // give 16 tiles).  The number of chunks is then rounded up to whole chunk
-// groups where that costs little: with 38 chunks at V = 151,936 the last
+// groups where that adds a third at most: with 38 chunks at V = 151,936 the last
 // group's blocks held 24 items, so the runs of 32 that an XCD takes straddled
-// three of them (work_item); 65,024 rows at d = 2048 ran 1 % slower than with
-// 40, 345,722 rows at d = 4096 0.1 to 0.2 %, which is within the noise.
+// three of them (work_item).  Whole calls, rounded against not: 65,024 rows,
+// d 2048, V 151,936 (38 -> 40) 0.994, 345,722 rows, d 4096 (38 -> 40) 0.999;
+// 200,000 rows, d 256, V 40,000 (12 -> 16) 0.98; 300,000 rows, d 512, V 50,257
+// (13 -> 16) 1.01; but 262,144 rows, V 32,000 (9 -> 16) 1.015 at d 256 and 1024.
 inline int64_t default_tpc(int64_t rows, int64_t n_vt) {
   int64_t tpc = ceil_div(rows, kTileN) * n_vt / 8192;
   if (tpc < 1) tpc = 1;
   if (tpc > 16) tpc = 16;
   const int64_t n_ch = ceil_div(n_vt, tpc);
-  return n_ch > kGroupCH ? ceil_div(n_vt, ceil_div(n_ch, kGroupCH) * kGroupCH) : tpc;
+  const int64_t whole = ceil_div(n_ch, kGroupCH) * kGroupCH;
+  return n_ch > kGroupCH && 3 * whole <= 4 * n_ch ? ceil_div(n_vt, whole) : tpc;
 }
 
 // Workspace layout for launches of at most `rows` rows with n_ch chunks.
