@@ -791,27 +791,30 @@ __global__ __launch_bounds__(kThreads, 1) void lmhead_logprob_kernel(LmheadArgs 
 // log p = z_y - (m + ln s); non-finite or out-of-range tokens give NaN.
 // With entropy requested (ENT), also H = ln s - E_p[z - m] = ln s - ln(2) t / s.
 //
-// Bound by the latency of the partials' loads, since few rows come with many
-// chunks (594 chunks of one vocabulary tile up to 3,500 rows at V = 151,936):
-// one thread per row walking all of them took 255 us for 96 rows x 594
-// chunks, 314 us for 1,554 x 594, 77 us for 3,333 x 197 and 24 us for
-// 65,024 x 38.  So a workgroup is kMergeRows rows x SEG chunk
-// segments: segment s takes chunks s, s + SEG, ... in order, kMergeRows
-// neighbouring rows per load, four chunks' loads in flight, and the segments'
-// states are then combined in order by the row's first thread: 247 us less
-// for the 96-row call (787 -> 540 us), 312 us less for 1,554 rows.
-constexpr int kMergeRows = 32;
+// Few rows come with many chunks (594 of one vocabulary tile each up to 3,500
+// rows at V = 151,936) and are bound by the latency of the partials' loads: one
+// thread per row walking all of them took 255 us for 96 rows x 594 chunks, 314 us
+// for 1,554 x 594, 77 us for 3,333 x 197.  So a workgroup is 32 rows x SEG chunk
+// segments: segment s takes chunks s, s + SEG, ... in order, neighbouring rows
+// per load, four chunks' loads in flight, and the segments' states are then
+// combined in order by the row's first thread: 247 us less for the 96-row call
+// (787 -> 540 us), 312 us less for 1,554 rows.  Many rows are bound by memory and
+// by the combining: one thread per row (ROWS 256, SEG 1), us against 8 segments:
+// 65,024 x 40 11.8 against 8.5, 131,072 x 38 13.2 against 13.2 (with the entropy
+// 14.8 against 17.3), 262,144 x 4 7.0 against 9.0, 345,722 x 40 30.2 against 48.1
+// (5.5 TB/s).
+constexpr int64_t kMergeManyRows = int64_t{1} << 17;
 
-template <int SEG, bool ENT>
-__global__ __launch_bounds__(kMergeRows * SEG) void merge_kernel(LmheadArgs p, float* __restrict__ logp,
+template <int ROWS, int SEG, bool ENT>
+__global__ __launch_bounds__(ROWS * SEG) void merge_kernel(LmheadArgs p, float* __restrict__ logp,
                                                                  float* __restrict__ lse_out,
                                                                  float* __restrict__ entropy) {
-  __shared__ float xm[SEG][kMergeRows], xs[SEG][kMergeRows], xz[SEG][kMergeRows], xt[ENT ? SEG : 1][kMergeRows];
-  const int r = threadIdx.x % kMergeRows;
-  const int seg = threadIdx.x / kMergeRows;
+  __shared__ float xm[SEG][ROWS], xs[SEG][ROWS], xz[SEG][ROWS], xt[ENT ? SEG : 1][ROWS];
+  const int r = threadIdx.x % ROWS;
+  const int seg = threadIdx.x / ROWS;
   const int64_t n_s = *p.n_scored;
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * kMergeRows + r;
-  if (static_cast<int64_t>(blockIdx.x) * kMergeRows >= n_s) return;   // (the whole workgroup)
+  const int64_t e = static_cast<int64_t>(blockIdx.x) * ROWS + r;
+  if (static_cast<int64_t>(blockIdx.x) * ROWS >= n_s) return;   // (the whole workgroup)
   float m = kNegInf, s = 0.f, z = kNegInf, t = 0.f;
   if (e < n_s) {
     constexpr int kBatch = 4;
@@ -891,11 +894,17 @@ hipError_t launch_lmhead_grad(const LmheadArgs& a, int64_t grid, hipStream_t str
   return hipGetLastError();
 }
 
+template <int ROWS, int SEG>
+static void run_merge(const LmheadArgs& a, int64_t n_rows, float* logp, float* lse, float* entropy,
+                      hipStream_t stream) {
+  const dim3 g(static_cast<unsigned>(ceil_div(n_rows, ROWS))), b(ROWS * SEG);
+  if (entropy) hipLaunchKernelGGL((merge_kernel<ROWS, SEG, true>), g, b, 0, stream, a, logp, lse, entropy);
+  else hipLaunchKernelGGL((merge_kernel<ROWS, SEG, false>), g, b, 0, stream, a, logp, lse, entropy);
+}
+
 hipError_t launch_merge(const LmheadArgs& a, int64_t n_rows, float* logp, float* lse,
                         float* entropy, hipStream_t stream) {
-  const int64_t blocks = (n_rows + kMergeRows - 1) / kMergeRows;
-  if (blocks <= 0) return hipSuccess;
-  const dim3 g(static_cast<unsigned>(blocks));
+  if (n_rows <= 0) return hipSuccess;
   // 8 or 32 segments per row.  32 shorten the chain of loads at the cost of more
   // LDS states and more steps for the row's first thread, more so with the
   // entropy's larger states; the line is the same with it, since it decides the
@@ -905,14 +914,9 @@ hipError_t launch_merge(const LmheadArgs& a, int64_t n_rows, float* logp, float*
   // 77.0 -> 77.7 at 64, 111.4 -> 111.6 at 96, 469 -> 466 at 594; with the entropy
   // 512 rows 19.1 -> 22.3 at 64, 27.7 -> 29.8 at 120, 37.7 -> 37.1 at 256, 73 ->
   // 67 at 594.
-  const bool wide = a.n_ch >= 96;
-  if (entropy) {
-    if (wide) hipLaunchKernelGGL((merge_kernel<32, true>), g, dim3(kMergeRows * 32), 0, stream, a, logp, lse, entropy);
-    else hipLaunchKernelGGL((merge_kernel<8, true>), g, dim3(kMergeRows * 8), 0, stream, a, logp, lse, entropy);
-  } else {
-    if (wide) hipLaunchKernelGGL((merge_kernel<32, false>), g, dim3(kMergeRows * 32), 0, stream, a, logp, lse, entropy);
-    else hipLaunchKernelGGL((merge_kernel<8, false>), g, dim3(kMergeRows * 8), 0, stream, a, logp, lse, entropy);
-  }
+  if (n_rows >= kMergeManyRows) run_merge<256, 1>(a, n_rows, logp, lse, entropy, stream);
+  else if (a.n_ch >= 96) run_merge<32, 32>(a, n_rows, logp, lse, entropy, stream);
+  else run_merge<32, 8>(a, n_rows, logp, lse, entropy, stream);
   return hipGetLastError();
 }
 

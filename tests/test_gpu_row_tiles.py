@@ -73,3 +73,22 @@ def test_merge_segments(hdl, chunks, n):
     logp, lse, _ = hdl.token_logprobs(H.cuda(), W.cuda(), y.cuda(), None, want_entropy=True)
     assert torch.equal(plain[0], logp) and torch.equal(plain[1], lse)
     assert np.abs(logp.cpu().numpy() - ref_p).max() <= 2e-3 and np.abs(lse.cpu().numpy() - ref_l).max() <= 2e-3
+
+
+# and its form for many rows (131,072 of the call and more), few of them scored
+# or all: every row's segments are one thread's
+@pytest.mark.parametrize("masked", [False, True])
+@pytest.mark.parametrize("n", [131071, 131077])
+def test_merge_many_rows(hdl, n, masked):
+    H, W, y = _inputs(n, 16, 256 * 10 - 3, torch.bfloat16, seed=n)
+    mask = (torch.rand(n, generator=torch.Generator().manual_seed(n)) < 0.03).to(torch.uint8) if masked else None
+    args = (H.cuda(), W.cuda(), y.cuda(), None if mask is None else mask.cuda())
+    plain = hdl.token_logprobs(*args)
+    logp, lse, _ = hdl.token_logprobs(*args, want_entropy=True)
+    assert torch.equal(plain[0], logp) and torch.equal(plain[1], lse)
+    on = torch.ones(n, dtype=torch.bool) if mask is None else mask != 0
+    assert not logp.cpu()[~on].any() and not lse.cpu()[~on].any()
+    at = torch.nonzero(on).view(-1)
+    at = torch.cat([at[:300], at[-300:]])
+    ref_p, ref_l = O.token_logprobs(as_f64(H[at]), as_f64(W), y[at].numpy())
+    assert np.abs(logp.cpu()[at].numpy() - ref_p).max() <= 2e-3 and np.abs(lse.cpu()[at].numpy() - ref_l).max() <= 2e-3
