@@ -143,27 +143,29 @@ inline bool make_plan_bounded(int64_t n_rows_total, int64_t vocab, int64_t d, in
 //    100,000, 300 rows) to 1.18 (V = 151,936, 340 rows).  fp32 tiles split W's
 //    values on the vector ALU for every row tile anew: 1.03 to 1.06 above 256
 //    rows, 1.3 below (V = 120,000), so they stay whole;
-//  - of half or a quarter where there would be fewer items than CUs (more row
-//    tiles read W more often, but into CUs that would idle).
+//  - of half or a quarter where their items still run at once, one on a CU: a
+//    half tile takes 0.55 of a whole one's time (fp32 0.65), so with a second
+//    round of workgroups little would be gained.  Whole calls against narrower
+//    tiles wherever there were fewer items than CUs (in brackets: whole tiles'
+//    items): bf16, d 2048, V 4,096: 600 rows (48) 0.99, 1,100 (80) 0.80, 2,500
+//    (160) 0.93, 3,500 (224) 0.90; V 32,000, 200 rows (125) 0.80; fp32, d 1024,
+//    the same rows 1.0, 0.71, 0.77, 0.77 and 0.72.
 __host__ __device__ inline ItemGrid item_grid(int64_t n_s, int64_t n_ch, bool bf16) {
   int64_t rows = bf16 && n_s <= kTileN / 2 * 3 ? kTileN / 2 : kTileN;
-  while (rows > kTileN / 4 && ceil_div(n_s, rows) * n_ch < kNumCu) rows /= 2;
+  while (rows > kTileN / 4 && ceil_div(n_s, rows / 2) * n_ch <= kNumCu) rows /= 2;
   return ItemGrid{ceil_div(n_s, rows), n_ch, rows};
 }
 
 // Workgroups of one launch over n rows (n <= plan.n_rows) with the call's
 // chunking: one for every item of any n_s <= n, i.e. whole tiles, at most three
-// half tiles, or, where those are fewer than kNumCu items, narrower ones (at
-// most four times as many).
+// half tiles, or up to kNumCu (which is less than a round) narrower ones.
 inline int64_t launch_grid(const LmheadPlan& p, int64_t n) {
   const int64_t halves = ceil_div(n, kTileN / 2);
   int64_t tiles = ceil_div(n, kTileN);
   if (tiles < (halves < 3 ? halves : 3)) tiles = halves < 3 ? halves : 3;
-  int64_t narrow = ceil_div(n, kTileN / 4) * p.n_ch;
-  if (narrow > 4 * kNumCu) narrow = 4 * kNumCu;
-  const int64_t items = tiles * p.n_ch > narrow ? tiles * p.n_ch : narrow;
   const int64_t round = kNumXcd * kGroupRT * kGroupCH;
-  return ceil_div(items, round) * round;
+  static_assert(kNumXcd * kGroupRT * kGroupCH >= kNumCu, "the narrow items fit the smallest grid");
+  return ceil_div(tiles * p.n_ch, round) * round;
 }
 
 // Work item of workgroup b.  The items are put in an order in which any 32
