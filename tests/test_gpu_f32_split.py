@@ -32,7 +32,7 @@ def test_fp32_rounding(hdl, n, d, V):
     logp, lse = hdl.token_logprobs(H.cuda(), W.cuda(), y.cuda())
     ref_p, ref_l = O.token_logprobs(as_f64(H), as_f64(W), y.numpy())
     # what d fp32 additions in any order can lose of a logit (u = 2^-24 each,
-    # the exactly split products counted as one more), plus the normaliser's
+    # what the split leaves out of the products counted as one more), plus the normaliser's
     # exp, sum and log: 64 u of the result's size
     mag = (as_f64(H)[:, None, :].__abs__() * np.abs(as_f64(W))[None]).sum(2).max(1)
     tol = 2.0 ** -24 * ((d + 1) * mag + 64 * (1 + np.abs(ref_l)))
